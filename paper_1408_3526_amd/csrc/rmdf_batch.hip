@@ -235,7 +235,7 @@ static hipError_t rebuild(rmdf_batch* b) {
     d.kind = kind_of(c);
     d.ring = rmdf_internal_ring(c, &d.nring, &d.dt);
     d.hw = (long long)a.H * a.W;
-    const int cols = (d.kind == KIND_16W) ? 4 : (d.kind == KIND_884 ? 8 : (d.kind == KIND_995 ? 4 : 2));
+    const int cols = (d.kind == KIND_16W) ? p16::WAVES : (d.kind == KIND_884 ? Shape<8, 8, 4>::PPB : (d.kind == KIND_995 ? Shape<9, 9, 5>::PPB : Shape<16, 16, 8>::PPB));
     const int xblocks = (a.W + cols - 1) / cols, yblocks = (a.H + a.TY - 1) / a.TY;
     int mx, my, mz, v;
     rmdf_internal_shape(c, &mx, &my, &mz, &v);

@@ -6,6 +6,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "rmdf_kernels.h"
 #include "rmdf_refine.h"
 #include "rmdf_wave.h"
@@ -20,12 +22,34 @@ static __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 static __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 static __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 
-// Workgroup barrier that orders LDS only: outstanding global loads (the
-// prefetch of the next row's observer state) stay in flight across it.
-static __device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+// Element at a byte offset from a base that is the same in all lanes: a 32-bit
+// offset per lane instead of a 64-bit address.
+template <class T>
+static __device__ __forceinline__ const T& at(const T* base, unsigned bytes) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+template <class T>
+static __device__ __forceinline__ T& at(T* base, unsigned bytes) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
+}
+
+// A column of N complex values in LDS at a 16-byte aligned address: 16-byte
+// accesses, the last value of an odd N alone.
+template <int N>
+static __device__ __forceinline__ void ld_col(const lds_v2* p, float2 (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k + 1 < N; k += 2) {
+    const float4 q = ld4(p + k);
+    v[k] = make_float2(q.x, q.y);
+    v[k + 1] = make_float2(q.z, q.w);
+  }
+  if (N % 2) v[N - 1] = ld2(p + N - 1);
+}
+template <int N>
+static __device__ __forceinline__ void st_col(lds_v2* p, const float2 (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k + 1 < N; k += 2) st4(p + k, v[k].x, v[k].y, v[k + 1].x, v[k + 1].y);
+  if (N % 2) st2(p + N - 1, v[N - 1]);
 }
 
 template <int MX>
@@ -144,21 +168,43 @@ static __device__ void row_chunk(const float* __restrict__ f, float2* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Per-pixel kernel.
+// Per-pixel kernel (generic: every compiled window shape).
+//
+// A wavefront owns PPW anchors (one, or two of the 8x8x4 window) and walks
+// down a tile of rows; the four wavefronts of a workgroup share only the
+// weight tables.  A lane holds CPL (plane, ky) columns of the Hermitian half
+// of its anchor's spectrum.  Since no stage leaves its wavefront, there is no
+// workgroup barrier after the tables; a row's smoothed R is loaded before the
+// flow stages instead of inside the candidate loop (one memory latency a row
+// instead of one per 64 candidates), and the planes beyond the half spectrum
+// are stored as mirrors so that the Hann pass along kx reads fixed offsets.
+// Against the form with workgroup barriers and loads in the candidate loop
+// (us per frame, output and velocity read): 9x9x5 640x512 941 -> 527 (VALU 69%
+// busy, 659 instructions an anchor; the state and R traffic alone would take
+// 370), 8x8x4 640x512 397 -> 241, 16x16x8 319x241 with 33x33 candidates
+// 1243 -> 714, the paper's 64x64 frames 24.4 -> 21.4.
 template <int MX, int MY, int MZ>
 struct Shape {
   static constexpr bool EVEN = (MX % 2 == 0);
   static constexpr int NP = EVEN ? MX / 2 : (MX + 1) / 2;   // stored kx planes
   static constexpr int NXH = MX / 2 + 1;                    // kx = 0 .. Mx/2
   static constexpr int NCOL = NP * MY;                      // (plane, ky) columns
-  static constexpr int NCOLP = NCOL <= 32 ? 32 : (NCOL <= 64 ? 64 : (NCOL <= 128 ? 128 : 256));
-  static constexpr int PPB = 256 / NCOLP;                   // pixels per block row-step
-  static constexpr int A_ELEMS = PPB * NCOL * MZ;           // Hann staging (float2)
-  static constexpr int QT_ELEMS = PPB * NXH * (MY + NVY_MAX);
-  static constexpr int U_ELEMS = A_ELEMS > QT_ELEMS ? A_ELEMS : QT_ELEMS;
-  static constexpr int TAB_ELEMS = NVY_MAX * MY + NVX_MAX * NXH;  // tau_y and tau_x, staged per tile
-  static constexpr size_t SMEM = sizeof(float2) * (U_ELEMS + A_ELEMS + 2 * MZ + MY + TAB_ELEMS) +
-                                 (sizeof(float) + sizeof(int)) * 256;
+  static constexpr int LPP = NCOL <= 32 ? 32 : 64;          // lanes per anchor
+  static constexpr int CPL = (NCOL + 63) / 64;              // columns per lane
+  static constexpr int PPW = 64 / LPP;                      // anchors per wavefront
+  static constexpr int WAVES = 4;
+  static constexpr int PPB = WAVES * PPW;                   // anchors per workgroup
+  // LDS rows are padded so that neighbouring lanes' 16-byte accesses fall on
+  // distinct banks (row strides of 12, 20 and 36 words over 64 banks)
+  static constexpr int MZP = MZ == 8 ? 10 : 6;              // a staged column's kz values
+  static constexpr int MYQ = (MY + 1) / 2 * 2;              // Q row (one kx)
+  static constexpr int MYT = MY == 16 ? 18 : 10;            // weights of one l_y
+  static constexpr int NXT = NXH == 9 ? 10 : 6;             // T row (one l_y); weights of one l_x
+  static constexpr int S_ELEMS = (NXH + 2) * MY * MZP;      // staged planes kx = -1 .. Mx/2 + 1 (float2)
+  static constexpr int QT_ELEMS = NXH * MYQ + NVY_MAX * NXT;
+  static constexpr int W_ELEMS = PPW * (S_ELEMS > QT_ELEMS ? S_ELEMS : QT_ELEMS);   // per wavefront
+  static constexpr int TAB_ELEMS = NVY_MAX * MYT + NVX_MAX * NXT + MYQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;
+  static constexpr size_t SMEM = sizeof(float2) * (TAB_ELEMS + WAVES * W_ELEMS);
 };
 
 
@@ -185,301 +231,459 @@ static __device__ __forceinline__ float2 coeff_at(int kx, int ky, int kz, float 
 
 // One work tile: PPB adjacent anchor columns starting at xb*PPB, rows
 // [yb*TY, yb*TY + TY).  All 256 threads of the block must call it.
-template <int MX, int MY, int MZ>
+// REFINED: velocity mode 3 (its eq. 8 per bin needs many registers).
+template <int MX, int MY, int MZ, bool REFINED = false>
 static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float* ring_delayed, int xb, int yb, char* smem) {
   using SH = Shape<MX, MY, MZ>;
-  constexpr int NP = SH::NP, NXH = SH::NXH, NCOL = SH::NCOL, NCOLP = SH::NCOLP, PPB = SH::PPB;
+  constexpr int NP = SH::NP, NXH = SH::NXH, NCOL = SH::NCOL, LPP = SH::LPP, CPL = SH::CPL, PPW = SH::PPW;
+  constexpr int MZP = SH::MZP, MYQ = SH::MYQ, MYT = SH::MYT, NXT = SH::NXT;
   constexpr bool EVEN = SH::EVEN;
 
-  float2* s_u = reinterpret_cast<float2*>(smem);  // Hann-z stage, later Q and T
-  float2* s_b = s_u + SH::U_ELEMS;                 // Hann-y stage
-  float2* s_twz = s_b + SH::A_ELEMS;
-  float2* s_twA = s_twz + MZ;
-  float2* s_twy = s_twA + MZ;
-  float2* s_tauy = s_twy + MY;                   // [nvy][MY]
-  float2* s_taux = s_tauy + NVY_MAX * MY;        // [nvx][NXH]
-  float* s_rv = reinterpret_cast<float*>(s_taux + NVX_MAX * NXH);
-  int* s_ri = reinterpret_cast<int*>(s_rv + 256);
+  lds_v2* s_tauy = (lds_v2*)smem;                // [nvy][MYT]
+  lds_v2* s_taux = s_tauy + NVY_MAX * MYT;       // [nvx][NXT]
+  lds_v2* s_twy = s_taux + NVX_MAX * NXT;        // [MY]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ps = (PPW == 1) ? 0 : lane / LPP;
+  const int cl = (PPW == 1) ? lane : lane % LPP;           // lane within the anchor
+  lds_float* s_gx = (lds_float*)(s_twy + MYQ);   // [nvx], then gy [nvy]
+  lds_v2* s_w = s_twy + MYQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2 + wv * SH::W_ELEMS + ps * (SH::W_ELEMS / PPW);
+  const int nvx = a.nvx, nvy = a.nvy, nv = a.nv;
+  for (int i = tid; i < MY; i += 256) s_twy[i] = v2f{a.twy[i].x, a.twy[i].y};
+  for (int i = tid; i < nvy * MY; i += 256) s_tauy[i / MY * MYT + i % MY] = v2f{a.tauy[i].x, a.tauy[i].y};
+  for (int i = tid; i < nvx * NXH; i += 256) s_taux[i / NXH * NXT + i % NXH] = v2f{a.taux[i].x, a.taux[i].y};
+  for (int i = tid; i < nvx + nvy; i += 256) s_gx[i] = (i < nvx) ? a.gx[i] : a.gy[i - nvx];
+  __syncthreads();                               // the only workgroup barrier
 
-  const int tid = threadIdx.x;
-  const int ps = tid / NCOLP, c = tid % NCOLP;
-  const int x = xb * PPB + ps;
-  const bool px_ok = x < a.W;
-  const bool col_ok = px_ok && c < NCOL;
-  const int p = c / MY, ky = c % MY;
   const int y0 = yb * a.TY;
   const int y1 = min(a.H, y0 + a.TY);
+  const int xw = xb * SH::PPB + wv * PPW;         // the wavefront's first anchor
+  if (xw >= a.W || y0 >= y1) return;             // whole wavefront leaves
+  // the second anchor of a pair past the frame's edge repeats the last column
+  // without storing; lanes past the last column repeat it
+  const bool px_ok = xw + ps < a.W;
+  const int dxw = px_ok ? ps : a.W - 1 - xw;
+  const int x = xw + dxw;
+  int p[CPL], ky[CPL], col[CPL];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) {
+    col[j] = min(cl + 64 * j, NCOL - 1);
+    p[j] = col[j] / MY;
+    ky[j] = col[j] % MY;
+  }
+  // addresses: a base per row (the same in all lanes) and a 32-bit offset per lane
+  unsigned so[CPL], ro[CPL];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) {
+    so[j] = (unsigned)((dxw * NCOL + col[j]) * MZ) * 8u;
+    ro[j] = (unsigned)(dxw * NP + p[j]) * 8u;
+  }
+  const unsigned qo = (unsigned)(dxw * nv) * 4u;
+  const bool st_ok = px_ok && cl < NCOL;         // (CPL > 1: every lane's columns exist)
 
-  for (int i = tid; i < MZ; i += 256) { s_twz[i] = a.twz[i]; s_twA[i] = a.twA[i]; }
-  for (int i = tid; i < MY; i += 256) s_twy[i] = a.twy[i];
-  // the stage B and C weight tables too: read there once per candidate and
-  // row, from LDS they add no global-load latency to every row's flow
-  for (int i = tid; i < a.nvy * MY; i += 256) s_tauy[i] = a.tauy[i];
-  for (int i = tid; i < a.nvx * NXH; i += 256) s_taux[i] = a.taux[i];
-  __syncthreads();
-
-  float2* s_a = s_u;                                   // [PPB][NCOL][MZ]
-  float2* s_q = s_u;                                   // [PPB][NXH][MY]
-  float2* s_t = s_u + PPB * NXH * MY;                  // [PPB][NXH][NVY_MAX]
-  const int nvx = a.nvx, nvy = a.nvy, nv = a.nv;
+  // Staged planes: (kx in [-1, NXH], ky, kz) at s_w[((kx + 1) * MY + ky) * MZP + kz]
+  auto sidx = [](int kx, int kyy) { return ((kx + 1) * MY + kyy) * MZP; };
+  lds_v2* s_q = s_w;                             // [NXH][MYQ] after Hann along kx
+  lds_v2* s_t = s_w + NXH * MYQ;                 // [nvy][NXT]
 
   // Column sliding DFT: seed with the direct DFT of the My rows above y0
   // (rows above the frame count as zero).  All My loads are issued before the
   // sum, so a tile start costs one memory latency, not My of them.
-  float2 acol = make_float2(0.f, 0.f);
-  if (col_ok) {
+  float2 acol[CPL], wy[CPL];
+#pragma unroll
+  for (int j = 0; j < CPL; ++j) {
     float2 v[MY];
 #pragma unroll
     for (int m = 0; m < MY; ++m) {
       const int yy = y0 - 1 - m;
-      v[m] = (yy >= 0) ? a.rs[((size_t)yy * a.W + x) * NP + p] : make_float2(0.f, 0.f);
+      v[m] = (yy >= 0) ? at(a.rs + ((size_t)yy * a.W + xw) * NP, ro[j]) : make_float2(0.f, 0.f);
     }
+    acol[j] = make_float2(0.f, 0.f);
+    int e = 0;                                   // (ky m) mod My
 #pragma unroll
-    for (int m = 0; m < MY; ++m) acol = cadd(acol, cmul(s_twy[(ky * m) % MY], v[m]));
+    for (int m = 0; m < MY; ++m) {
+      acol[j] = cadd(acol[j], cmul(ld2(&s_twy[e]), v[m]));
+      e += ky[j];
+      e = (e >= MY) ? e - MY : e;
+    }
+    wy[j] = ld2(&s_twy[ky[j]]);
   }
-  const float2 wy = s_twy[ky % MY];
 
-  float2 X[MZ];
-  if (col_ok && y0 < y1) {
-    const float2* src = a.st + (((size_t)y0 * a.W + x) * NCOL + c) * MZ;
+  // the same in every lane: held in scalar registers
+  auto uni = [](float2 v) {
+    return make_float2(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v.x))),
+                       __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v.y))));
+  };
+  float2 twz[MZ], twA[MZ];
 #pragma unroll
-    for (int k = 0; k < MZ; ++k) X[k] = src[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < MZ; ++k) X[k] = make_float2(0.f, 0.f);
+  for (int k = 0; k < MZ; ++k) {
+    twz[k] = uni(a.twz[k]);
+    twA[k] = uni(a.twA[k]);
   }
+
+  // first row's state and row-spectrum samples; later rows' are loaded one
+  // row ahead
+  float2 Xn[CPL][MZ], in_n[CPL], in_o[CPL];
+  auto load_row = [&](int y) {
+    const float2* src = a.st + ((size_t)y * a.W + xw) * (NCOL * MZ);
+    const float2* rn = a.rs + ((size_t)y * a.W + xw) * NP;
+    const float2* rl = a.rs + ((size_t)max(y - MY, 0) * a.W + xw) * NP;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+#pragma unroll
+      for (int k = 0; k < MZ; ++k) Xn[j][k] = at(src, so[j] + 8u * k);
+      in_n[j] = at(rn, ro[j]);
+      in_o[j] = at(rl, ro[j]);
+    }
+  };
+  load_row(y0);
+
+  // The lane's place in stages B (item kx * nvy + iy) and C (item iy * nvx + ix).
+  // One column per lane: items cl, cl + LPP, ..., the pair of indices moving by
+  // (LPP / n, LPP % n) with a carry.  Two columns per lane (MX = 16): a weight or
+  // T row is 128 or 72 bytes, and the LDS return path, not the FMAs, bounds
+  // stages that read two rows per item; so LB lanes per kx share a Q row over
+  // the l_y they take (g, g + LB, ...), and a T row serves KX = 3 candidates of
+  // one l_y, LC = ceil(nvx / 3) apart, G l_y at a time (319x241, 33x33
+  // candidates: 733 against 890 us a frame; the small windows' flat order is
+  // 8 to 10% faster than this one).
+  constexpr bool ROWS = CPL > 1;
+  constexpr int LB = LPP / NXH, KX = 3;
+  const int kxB = ROWS ? cl / LB : cl / nvy, iyB = ROWS ? cl - kxB * LB : cl - kxB * nvy;
+  const int dkB = LPP / nvy, diB = LPP - dkB * nvy;
+  const int LC = ROWS ? (nvx + KX - 1) / KX : nvx, G = LPP / LC;
+  const int iyC0 = cl / LC, ixC0 = cl - iyC0 * LC;
+  const int dxC = LPP - G * LC;                  // (one column per lane)
+  const int o_q = kxB * MYQ, o_ty = iyB * MYT, o_t = iyB * NXT + kxB, o_tC = iyC0 * NXT, o_xC = ixC0 * NXT;
+  const int t_last = (nvy - 1) * NXT;
+  constexpr int NB = 6;                          // candidates per lane whose smoothed R is loaded together
+  const float inv_nvx = 1.0f / (float)nvx;
 
   for (int y = y0; y < y1; ++y) {
-    const size_t pix = (size_t)y * a.W + x;
-    // ---- column sliding DFT: comb on the row spectra, resonator w_y^ky
-    if (col_ok) {
-      float2 in = a.rs[((size_t)y * a.W + x) * NP + p];
-      if (y >= MY) in = csub(in, a.rs[((size_t)(y - MY) * a.W + x) * NP + p]);
-      acol = cadd(cmul(wy, acol), in);
-    }
-    const float2 s2 = cscale(acol, a.inv_sqrt_my);
-
-    // ---- temporal deadbeat observer: prior = rotate(posterior), innovation
-    // e = input - sum(prior), posterior = prior + e / Mz
-    if (col_ok) {
+    const size_t pix0 = (size_t)y * a.W + xw;     // the same in all lanes
+    // opaque per row: what stage C derives from the lane's place is computed
+    // again each row instead of being held in registers across the loop
+    int iyC = iyC0, ixC = ixC0;
+    if (ROWS) asm volatile("" : "+v"(iyC), "+v"(ixC));
+    float2 X[CPL][MZ];
+    float* rp = a.rsm + pix0 * nv;
+    float rn[NB];
+    // smoothed R of the next NB candidates: from item w on, or (ROWS) NB / KX
+    // rounds from l_y = w on; places past the grid read its last value
+    auto load_r = [&](int w) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        rn[i] = at(rp, qo + 4u * (unsigned)min(ROWS ? (w + i / KX * G) * nvx + ixC + i % KX * LC : w + i * LPP, nv - 1));
+    };
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      // ---- column sliding DFT: comb on the row spectra, resonator w_y^ky
+      float2 in = in_n[j];
+      if (y >= MY) in = csub(in, in_o[j]);
+      acol[j] = cadd(cmul(wy[j], acol[j]), in);
+      const float2 s2 = cscale(acol[j], a.inv_sqrt_my);
+      // ---- temporal deadbeat observer: prior = rotate(posterior), innovation
+      // e = input - sum(prior), posterior = prior + e / Mz
       float2 sum = make_float2(0.f, 0.f);
 #pragma unroll
       for (int k = 0; k < MZ; ++k) {
-        X[k] = cmul(s_twz[k], X[k]);
-        sum = cadd(sum, X[k]);
+        X[j][k] = cmul(twz[k], Xn[j][k]);
+        sum = cadd(sum, X[j][k]);
       }
       const float2 e = cscale(csub(s2, sum), 1.0f / MZ);
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) X[k] = cadd(X[k], e);
-      float2* dst = a.st + (pix * NCOL + c) * MZ;
+      for (int k = 0; k < MZ; ++k) X[j][k] = cadd(X[j][k], e);
+      if (st_ok) {
+        float2* dst = a.st + pix0 * (NCOL * MZ);
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) dst[k] = X[k];
+        for (int k = 0; k < MZ; ++k) at(dst, so[j] + 8u * k) = X[j][k];
+      }
     }
-    // prefetch the next row's state (in flight during the flow stages)
-    float2 Xn[MZ];
-    if (col_ok && y + 1 < y1) {
-      const float2* src = a.st + ((pix + a.W) * NCOL + c) * MZ;
-#pragma unroll
-      for (int k = 0; k < MZ; ++k) Xn[k] = src[k];
-    } else {
-#pragma unroll
-      for (int k = 0; k < MZ; ++k) Xn[k] = make_float2(0.f, 0.f);
+    // this row's smoothed R (first rounds of stage C), the delayed sample and
+    // the next row's state are in flight during the flow stages; stage C waits
+    // for the first group only (vector memory completes in order)
+    load_r(ROWS ? iyC : cl);
+    float idel = 0.f;
+    {
+      const int xs = x - a.dx, ys = y - a.dy;
+      if (ring_delayed != nullptr && xs >= 0 && ys >= 0) idel = ring_delayed[(size_t)ys * a.W + xs];
     }
+    if (y + 1 < y1) load_row(y + 1);
 
     // ---- high-pass (drop kx = ky = 0 for every kz) and Hann along kz.
     // Hann along an axis is Y(k) = (2X(k) - X(k-1) - X(k+1)) / 4; the 1/4 per
     // axis is folded into the stage-A weights.
-    lds_barrier();     // the previous row's stage C has finished reading s_u
-    if (col_ok) {
+    float2 Hy[CPL][MZ];
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
       float2 V[MZ];
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) V[k] = X[k];
-      if (p == 0 && ky == 0) {
-        if (EVEN) {
-          // packed plane holds S(0) + j S(Mx/2); remove the S(0) part only:
-          // S(0)(0, kz) = (C(kz) + conj C(-kz)) / 2
+      for (int k = 0; k < MZ; ++k) V[k] = X[j][k];
+      if (col[j] == 0) {
 #pragma unroll
-          for (int k = 0; k < MZ; ++k) {
-            const float2 cm = X[(MZ - k) % MZ];
-            V[k] = make_float2(0.5f * (X[k].x - cm.x), 0.5f * (X[k].y + cm.y));
-          }
-        } else {
-#pragma unroll
-          for (int k = 0; k < MZ; ++k) V[k] = make_float2(0.f, 0.f);
+        for (int k = 0; k < MZ; ++k) {
+          // even Mx: the packed plane holds S(0) + j S(Mx/2); remove the S(0)
+          // part only: S(0)(0, kz) = (C(kz) + conj C(-kz)) / 2
+          const float2 cm = X[j][(MZ - k) % MZ];
+          V[k] = EVEN ? make_float2(0.5f * (X[j][k].x - cm.x), 0.5f * (X[j][k].y + cm.y)) : make_float2(0.f, 0.f);
         }
       }
-      float2* dst = s_a + (ps * NCOL + c) * MZ;
 #pragma unroll
       for (int k = 0; k < MZ; ++k) {
         const float2 l = V[(k + MZ - 1) % MZ], r = V[(k + 1) % MZ];
-        dst[k] = make_float2(2.f * V[k].x - l.x - r.x, 2.f * V[k].y - l.y - r.y);
+        Hy[j][k] = make_float2(2.f * V[k].x - l.x - r.x, 2.f * V[k].y - l.y - r.y);
       }
     }
-    lds_barrier();
-    // ---- Hann along ky
-    float2 Hy[MZ];
-    if (col_ok) {
-      const float2* cur = s_a + (ps * NCOL + c) * MZ;
-      const float2* lo = s_a + (ps * NCOL + p * MY + (ky + MY - 1) % MY) * MZ;
-      const float2* hi = s_a + (ps * NCOL + p * MY + (ky + 1) % MY) * MZ;
+    // ---- Hann along ky: a plane of 16 ky is a row of 16 lanes (DPP); other
+    // windows exchange through the staging rows
+    if (MY == 16) {
+#pragma unroll
+      for (int j = 0; j < CPL; ++j)
+#pragma unroll
+        for (int k = 0; k < MZ; ++k) {
+          const float2 v = Hy[j][k];
+          const float2 l = make_float2(dppf<ROR1>(v.x), dppf<ROR1>(v.y));
+          const float2 r = make_float2(dppf<ROR15>(v.x), dppf<ROR15>(v.y));
+          Hy[j][k] = make_float2(2.f * v.x - l.x - r.x, 2.f * v.y - l.y - r.y);
+        }
+      wave_lds_sync();                           // the previous row's stage C reads are done
+    } else {
+      wave_lds_sync();
+      st_col<MZ>(s_w + sidx(p[0], ky[0]), Hy[0]);
+      wave_lds_sync();
+      float2 l[MZ], r[MZ];
+      ld_col<MZ>(s_w + sidx(p[0], ky[0] == 0 ? MY - 1 : ky[0] - 1), l);
+      ld_col<MZ>(s_w + sidx(p[0], ky[0] == MY - 1 ? 0 : ky[0] + 1), r);
 #pragma unroll
       for (int k = 0; k < MZ; ++k) {
-        const float2 v = cur[k], l = lo[k], r = hi[k];
-        Hy[k] = make_float2(2.f * v.x - l.x - r.x, 2.f * v.y - l.y - r.y);
+        const float2 v = Hy[0][k];
+        Hy[0][k] = make_float2(2.f * v.x - l[k].x - r[k].x, 2.f * v.y - l[k].y - r[k].y);
+      }
+      wave_lds_sync();                           // every lane has read its neighbours
+    }
+    // ---- stage the y,z-windowed planes; even Mx: unpack plane 0 with its
+    // (-ky, -kz) mirror, S(0) = (C + conj C(-k)) / 2, S(Mx/2) = (C - conj C(-k)) / 2j
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) st_col<MZ>(s_w + sidx(p[j], ky[j]), Hy[j]);
+    if (EVEN) {
+      wave_lds_sync();
+      if (cl < MY) {
+        float2 w[MZ], s0[MZ], sh[MZ];
+        ld_col<MZ>(s_w + sidx(0, ky[0] == 0 ? 0 : MY - ky[0]), w);
+#pragma unroll
+        for (int k = 0; k < MZ; ++k) {
+          const float2 u = Hy[0][k], m = w[(MZ - k) % MZ];
+          s0[k] = make_float2(0.5f * (u.x + m.x), 0.5f * (u.y - m.y));
+          sh[k] = make_float2(0.5f * (u.y + m.y), -0.5f * (u.x - m.x));
+        }
+        wave_lds_sync();                         // every read of plane 0 precedes every write to it
+        st_col<MZ>(s_w + sidx(0, ky[0]), s0);
+        st_col<MZ>(s_w + sidx(MX / 2, ky[0]), sh);
       }
     }
-    lds_barrier();     // everyone has read s_a (s_u is reused for Q below)
-    if (col_ok) {
-      float2* dst = s_b + (ps * NCOL + c) * MZ;
+    // planes -1 and NXH are the conjugate mirrors of planes 1 and MX - NXH:
+    // S(-kx, ky, kz) = conj S(kx, -ky, -kz)
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) dst[k] = Hy[k];
+    for (int j = 0; j < CPL; ++j) {
+      const bool lo = (p[j] == 1), hi = (p[j] == MX - NXH);
+      if (lo | hi) {
+        float2 m[MZ];
+#pragma unroll
+        for (int k = 0; k < MZ; ++k) m[k] = cconj(Hy[j][(MZ - k) % MZ]);
+        st_col<MZ>(s_w + sidx(lo ? -1 : NXH, ky[j] == 0 ? 0 : MY - ky[j]), m);
+      }
     }
-    lds_barrier();
+    wave_lds_sync();
 
     // ---- Hann along kx, power spectrum (eq. 9), stage A of eq. (10):
     // Q(kx, ky) = sum_kz P(k) w_z^kz (l_z = 1), kx in [0, Mx/2]
-    if (col_ok) {
-      const float2* B = s_b + ps * NCOL * MZ;
-      // y,z-windowed spectrum at any kx in [0, Mx) from the stored half
-      auto Vk = [&](int kx, int kyy, int kz) -> float2 {
-        bool cj = false;
-        if (2 * kx > MX) { kx = MX - kx; kyy = (MY - kyy) % MY; kz = (MZ - kz) % MZ; cj = true; }
-        float2 r;
-        if (kx == 0 || (EVEN && 2 * kx == MX)) {
-          const float2 u = B[kyy * MZ + kz];
-          if (!EVEN) {
-            r = u;
-          } else {
-            const float2 w = B[((MY - kyy) % MY) * MZ + (MZ - kz) % MZ];
-            if (kx == 0) r = make_float2(0.5f * (u.x + w.x), 0.5f * (u.y - w.y));
-            else         r = make_float2(0.5f * (u.y + w.y), -0.5f * (u.x - w.x));
-          }
-        } else {
-          r = B[(kx * MY + kyy) * MZ + kz];
-        }
-        return cj ? cconj(r) : r;
-      };
-      const int nk = (EVEN && p == 0) ? 2 : 1;
-      for (int j = 0; j < nk; ++j) {
-        const int kx = (j == 0) ? p : MX / 2;
-        float2 q = make_float2(0.f, 0.f);
+    auto stage_a = [&](int kx, int kyy) -> float2 {
+      float2 v[MZ], l[MZ], r[MZ];
+      ld_col<MZ>(s_w + sidx(kx, kyy), v);
+      ld_col<MZ>(s_w + sidx(kx - 1, kyy), l);
+      ld_col<MZ>(s_w + sidx(kx + 1, kyy), r);
+      float2 q = make_float2(0.f, 0.f);
 #pragma unroll
-        for (int kz = 0; kz < MZ; ++kz) {
-          const float2 v = Vk(kx, ky, kz);
-          const float2 l = Vk((kx + MX - 1) % MX, ky, kz);
-          const float2 r = Vk((kx + 1) % MX, ky, kz);
-          const float hx = 2.f * v.x - l.x - r.x, hy = 2.f * v.y - l.y - r.y;
-          const float P = hx * hx + hy * hy;
-          q.x += P * s_twA[kz].x;
-          q.y += P * s_twA[kz].y;
-        }
-        s_q[(ps * NXH + kx) * MY + ky] = q;
+      for (int k = 0; k < MZ; ++k) {
+        const float hx = 2.f * v[k].x - l[k].x - r[k].x, hy = 2.f * v[k].y - l[k].y - r[k].y;
+        const float P = hx * hx + hy * hy;
+        q.x += P * twA[k].x;
+        q.y += P * twA[k].y;
       }
+      return q;
+    };
+    float2 Q[CPL], Qh = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) Q[j] = stage_a(p[j], ky[j]);
+    if (EVEN) {
+      if (cl < MY) Qh = stage_a(MX / 2, ky[0]);
     }
-    lds_barrier();
+    wave_lds_sync();                             // the staged planes are read (Q and T alias them)
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) st2(&s_q[p[j] * MYQ + ky[j]], Q[j]);
+    if (EVEN) {
+      if (cl < MY) st2(&s_q[(MX / 2) * MYQ + ky[0]], Qh);
+    }
+    wave_lds_sync();
 
     // ---- stage B: T(kx, iy) = sum_ky Q(kx, ky) tau_y(ky, l_y[iy])
-    for (int w = c; w < NXH * nvy; w += NCOLP) {
-      const int kx = w / nvy, iy = w % nvy;
-      const float2* Q = s_q + (ps * NXH + kx) * MY;
-      const float2* ty = s_tauy + iy * MY;
-      float2 t = make_float2(0.f, 0.f);
+    {
+      float2 q[MY], ty[MY];
+      auto item = [&](const lds_v2* p_ty, lds_v2* p_t) {
+        ld_col<MY>(p_ty, ty);
+        float2 t = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int k = 0; k < MY; ++k) t = cadd(t, cmul(Q[k], ty[k]));
-      s_t[(ps * NXH + kx) * NVY_MAX + iy] = t;
+        for (int k = 0; k < MY; ++k) t = cadd(t, cmul(q[k], ty[k]));
+        st2(p_t, t);
+      };
+      // (LDS addresses move by additions: a 32-bit multiplication takes four
+      // issue slots)
+      const lds_v2 *p_q = s_q + o_q, *p_ty = s_tauy + o_ty;
+      lds_v2* p_t = s_t + o_t;
+      int kx = kxB, iy = iyB;
+      if (ROWS) {
+        if (kx < NXH) {
+          ld_col<MY>(p_q, q);
+          for (; iy < nvy; iy += LB, p_ty += LB * MYT, p_t += LB * NXT) item(p_ty, p_t);
+        }
+      } else {
+        while (kx < NXH) {
+          ld_col<MY>(p_q, q);
+          item(p_ty, p_t);
+          kx += dkB;
+          iy += diB;
+          p_q += dkB * MYQ;
+          p_ty += diB * MYT;
+          p_t += dkB + diB * NXT;
+          const int carry = (iy >= nvy) ? -1 : 0;
+          iy -= carry & nvy;
+          kx -= carry;
+          p_q += carry & MYQ;
+          p_ty -= carry & (nvy * MYT);
+          p_t += carry & (1 - nvy * NXT);
+        }
+      }
     }
-    lds_barrier();
+    wave_lds_sync();
 
     // ---- stage C: R(ix, iy) = sum_kx w(kx) Re[T(kx, iy) tau_x(kx, l_x[ix])],
     // first-order smoothing, running argmax
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    for (int w = c; w < nv; w += NCOLP) {
-      const int ix = w % nvx, iy = w / nvx;
-      const float2* tx = s_taux + ix * NXH;
-      float r = 0.f;
+    {
+      float2 t[NXH], tx[ROWS ? KX : 1][NXH];
+      auto item = [&](const float2 (&w_x)[NXH], float r_prev, int w) {
+        float r = 0.f;
 #pragma unroll
-      for (int kx = 0; kx < NXH; ++kx) {
-        const float2 t = s_t[(ps * NXH + kx) * NVY_MAX + iy];
-        r += t.x * tx[kx].x - t.y * tx[kx].y;
-      }
-      if (px_ok) {
-        float* rp = a.rsm + pix * nv + w;
-        const float sm = (1.f - a.alpha) * r + a.alpha * (*rp);
-        *rp = sm;
+        for (int kx = 0; kx < NXH; ++kx) r += t[kx].x * w_x[kx].x - t[kx].y * w_x[kx].y;
+        const float sm = (1.f - a.alpha) * r + a.alpha * r_prev;
+        if (px_ok) at(rp, qo + 4u * (unsigned)w) = sm;
         amax_merge(bv, bi, sm, w);
+      };
+      float rc[NB];
+      auto next = [&]() {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) rc[i] = rn[i];
+      };
+      if constexpr (ROWS) {
+#pragma unroll
+        for (int u = 0; u < KX; ++u) ld_col<NXH>(s_taux + min(ixC + u * LC, nvx - 1) * NXT, tx[u]);
+        for (int iy0 = 0; iy0 < nvy; iy0 += NB / KX * G) {
+          next();
+          if (iy0 + NB / KX * G < nvy) load_r(iy0 + NB / KX * G + iyC);
+#pragma unroll
+          for (int v = 0; v < NB / KX; ++v) {
+            const int iy = iy0 + v * G + iyC;
+            if (iyC < G && iy < nvy) {           // lanes past the last whole group idle
+              ld_col<NXH>(s_t + iy * NXT, t);
+#pragma unroll
+              for (int u = 0; u < KX; ++u)
+                if (ixC + u * LC < nvx) item(tx[u], rc[v * KX + u], iy * nvx + ixC + u * LC);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one round's LDS reads in flight at a time
+          }
+        }
+      } else {
+        int ix = ixC, o_t = o_tC;
+        const lds_v2* p_x = s_taux + o_xC;
+        for (int w0 = 0; w0 < nv; w0 += NB * LPP) {
+          next();
+          if (w0 + NB * LPP < nv) load_r(w0 + NB * LPP + cl);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            if (w0 + i * LPP < nv) {             // uniform: some lane has a candidate
+              ld_col<NXH>(s_t + min(o_t, t_last), t);
+              ld_col<NXH>(p_x, tx[0]);
+              const int w = w0 + i * LPP + cl;
+              if (w < nv) item(tx[0], rc[i], w);
+              ix += dxC;
+              const int carry = (ix >= nvx) ? -1 : 0;
+              ix -= carry & nvx;
+              o_t += G * NXT + (carry & NXT);
+              p_x += dxC * NXT - (carry & (nvx * NXT));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
     }
-    // reduce (value, index) over the pixel's NCOLP threads (within the
-    // wavefront by DPP and lane reads, across wavefronts through LDS)
-    group_amax<(NCOLP < 64 ? NCOLP : 64)>(bv, bi);
-    if (NCOLP > 64) {
-      s_rv[tid] = bv;
-      s_ri[tid] = bi;
-      lds_barrier();
-      for (int wv = 1; wv < NCOLP / 64; ++wv) amax_merge(bv, bi, s_rv[(tid ^ (wv * 64))], s_ri[(tid ^ (wv * 64))]);
-      lds_barrier();
-    }
+    group_amax<LPP>(bv, bi);
     const int istar = (bi < nv) ? bi : 0;   // no finite candidate: fall back to index 0
 
     // ---- velocity mode 3: refine the peak between grid points, from the
-    // smoothed R this row has just stored (the barrier makes the workgroup's
-    // global stores visible to all of its threads)
+    // smoothed R this row has just stored (the fence makes the wavefront's
+    // stores visible to all of its lanes)
     float2 vref = make_float2(0.f, 0.f);
-    if (a.vmode == 3) {
-      __syncthreads();
-      if (px_ok) {
-        const float* rp = a.rsm + pix * nv;
-        vref = refine_peak(a.gx, a.gy, nvx, nvy, istar, rp[istar], [&](int w) { return rp[w]; });
-      }
+    if (REFINED) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      vref = refine_peak(a.gx, a.gy, nvx, nvy, istar, at(rp, qo + 4u * (unsigned)istar),
+                         [&](int w) { return at(rp, qo + 4u * (unsigned)w); });
     }
 
     // ---- background estimate (eq. 4) with the coefficients of the chosen
     // velocity (eq. 8 at the bins; Hermitian weights folded into the table, or
     // evaluated here for the refined velocity)
     const int hsel = (a.vmode == 2) ? nv : istar;
-    float acc = 0.f;
-    if (col_ok && p <= a.bx) {
-      const int kyc = (2 * ky <= MY) ? ky : ky - MY;
-      if (kyc >= -a.by && kyc <= a.by) {
-        if (a.vmode == 3) {
-          const float wgt = (p == 0) ? 1.f : 2.f;
+    float tot = 0.f;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      float acc = 0.f;
+      const int kyc = (2 * ky[j] <= MY) ? ky[j] : ky[j] - MY;
+      if ((CPL > 1 || cl < NCOL) && p[j] <= a.bx && kyc >= -a.by && kyc <= a.by) {
+        if (REFINED) {
+          const float wgt = (p[j] == 0) ? 1.f : 2.f;
 #pragma unroll
           for (int kz = 0; kz < MZ; ++kz) {
-            const float2 h = coeff_at<MX, MY, MZ>(p, kyc, kz, vref.x, vref.y, a.dx, a.dy, a.dt);
-            acc += wgt * (h.x * X[kz].x - h.y * X[kz].y);
+            const float2 h = coeff_at<MX, MY, MZ>(p[j], kyc, kz, vref.x, vref.y, a.dx, a.dy, a.dt);
+            acc += wgt * (h.x * X[j][kz].x - h.y * X[j][kz].y);
           }
         } else {
-          const float2* h = a.htab + (((size_t)hsel * (a.bx + 1) + p) * (2 * a.by + 1) + (kyc + a.by)) * MZ;
+          // (at most (33^2 + 1) 8 17 8 entries)
+          const unsigned h0 = __umul24(__umul24(hsel, a.bx + 1) + p[j], 2 * a.by + 1) * (8u * MZ) + (kyc + a.by) * (8u * MZ);
 #pragma unroll
-          for (int kz = 0; kz < MZ; ++kz) acc += h[kz].x * X[kz].x - h[kz].y * X[kz].y;
+          for (int kz = 0; kz < MZ; ++kz) {
+            const float2 h = at(a.htab, h0 + 8u * kz);
+            acc += h.x * X[j][kz].x - h.y * X[j][kz].y;
+          }
         }
       }
+      tot += group_sum<LPP>(acc);
     }
-    acc = group_sum<(NCOLP < 64 ? NCOLP : 64)>(acc);
-    if (NCOLP > 64) {
-      s_rv[tid] = acc;
-      lds_barrier();
-      float tot = 0.f;
-      for (int wv = 0; wv < NCOLP / 64; ++wv) tot += s_rv[(ps * NCOLP) + wv * 64];
-      acc = tot;
-      lds_barrier();
-    }
-    if (px_ok && c == 0) {
-      const int xs = x - a.dx, ys = y - a.dy;
-      float idel = (ring_delayed != nullptr && xs >= 0 && ys >= 0) ? ring_delayed[(size_t)ys * a.W + xs] : 0.f;
+    if (px_ok && cl == 0) {
       if (!isfinite(idel)) idel = 0.f;
-      a.out[pix] = idel - acc;
+      const size_t pix = pix0 + ps;
+      a.out[pix] = idel - tot;
       if (a.vmode == 2) {
         a.vxy[pix] = make_float2(a.fvx, a.fvy);
         a.vidx[pix] = -1;
       } else {
-        a.vxy[pix] = (a.vmode == 3) ? vref : make_float2(a.gx[istar % nvx], a.gy[istar / nvx]);
+        const int iy = (int)(((float)istar + 0.5f) * inv_nvx);   // istar / nvx (below 2^11, so exact)
+        a.vxy[pix] = REFINED ? vref : make_float2(s_gx[istar - iy * nvx], s_gx[nvx + iy]);
         a.vidx[pix] = istar;
       }
     }
-#pragma unroll
-    for (int k = 0; k < MZ; ++k) X[k] = Xn[k];
   }
 }
 

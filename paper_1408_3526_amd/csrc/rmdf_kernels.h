@@ -57,7 +57,9 @@ struct PixArgs {
 
 bool shape_supported(int mx, int my, int mz);
 int planes_for(int mx);
-// anchors (columns) one workgroup of the generic pixel kernel covers per row
+// columns per tile that the default tile height of the generic kernel counts
+// with (a tile's height sets where the column recursion restarts, so this is
+// part of the results, not of the launch: Shape::PPB is what a workgroup takes)
 int pixel_block_columns(int mx, int my, int mz);
 // default rows per work tile for an H x W frame
 int auto_tile_rows(int H, int W, int block_columns);

@@ -41,12 +41,12 @@ __global__ void __launch_bounds__(256) k_row(const float* __restrict__ f, float2
   row_chunk<MX, DIRECT>(f, rs, twx, H, W, blockIdx.y, blockIdx.x * RCX, smem, nonfinite, slot);
 }
 
-template <int MX, int MY, int MZ>
-__global__ void __launch_bounds__(256) k_pixel(PixArgs a) {
+template <int MX, int MY, int MZ, bool REFINED>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MZ == 8 ? 2 : 4))) k_pixel(PixArgs a) {
   using SH = Shape<MX, MY, MZ>;
   __shared__ __align__(16) char smem[SH::SMEM];
   const int xblocks = (a.W + SH::PPB - 1) / SH::PPB;
-  pixel_tile<MX, MY, MZ>(a, a.ring_delayed, blockIdx.x % xblocks, blockIdx.x / xblocks, smem);
+  pixel_tile<MX, MY, MZ, REFINED>(a, a.ring_delayed, blockIdx.x % xblocks, blockIdx.x / xblocks, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -105,7 +105,8 @@ static hipError_t launch_pixel_t(const PixArgs& a, hipStream_t s) {
   using SH = Shape<MX, MY, MZ>;
   const int xblocks = (a.W + SH::PPB - 1) / SH::PPB;
   const int yblocks = (a.H + a.TY - 1) / a.TY;
-  hipLaunchKernelGGL((k_pixel<MX, MY, MZ>), dim3(xblocks * yblocks), dim3(256), 0, s, a);
+  if (a.vmode == 3) hipLaunchKernelGGL((k_pixel<MX, MY, MZ, true>), dim3(xblocks * yblocks), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_pixel<MX, MY, MZ, false>), dim3(xblocks * yblocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -133,9 +134,9 @@ bool shape_supported(int mx, int my, int mz) {
 int planes_for(int mx) { return (mx % 2 == 0) ? mx / 2 : (mx + 1) / 2; }
 
 int pixel_block_columns(int mx, int my, int mz) {
-  if (mx == 8 && my == 8 && mz == 4) return Shape<8, 8, 4>::PPB;
-  if (mx == 16 && my == 16 && mz == 8) return Shape<16, 16, 8>::PPB;
-  if (mx == 9 && my == 9 && mz == 5) return Shape<9, 9, 5>::PPB;
+  if (mx == 8 && my == 8 && mz == 4) return 8;
+  if (mx == 16 && my == 16 && mz == 8) return 2;
+  if (mx == 9 && my == 9 && mz == 5) return 4;
   return 1;
 }
 

@@ -42,22 +42,6 @@ constexpr int NV1_MAX = 21;       // 3 lane groups x 21 <= 64
 
 static __device__ __forceinline__ float2 f2(float x, float y) { return make_float2(x, y); }
 
-// LDS pointers keep their address space so every access is a ds_* instruction
-// with an immediate offset (a generic pointer would become a flat access)
-#define RMDF_LDS __attribute__((address_space(3)))
-#define RMDF_GLOBAL __attribute__((address_space(1)))
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef RMDF_LDS v2f lds_v2;
-typedef RMDF_LDS v4f lds_v4;
-typedef RMDF_LDS float lds_float;
-__device__ __forceinline__ float2 ld2(const lds_v2* p) { const v2f v = *p; return make_float2(v.x, v.y); }
-__device__ __forceinline__ float4 ld4(const lds_v2* p) {
-  const v4f v = *reinterpret_cast<const lds_v4*>(p);
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void st2(lds_v2* p, float2 v) { *p = v2f{v.x, v.y}; }
 // Observer-state traffic is streamed once per frame: non-temporal loads and
 // stores (measured 4% faster than cached ones for the whole kernel).
 __device__ __forceinline__ float4 ld_stream(const float4* p) {
@@ -74,9 +58,6 @@ __device__ __forceinline__ float2 ld2_stream(const float2* p) {
 __device__ __forceinline__ void st2_stream(float2* p, float2 v) {
   __builtin_nontemporal_store(v2f{v.x, v.y}, reinterpret_cast<v2f*>(p));
 }
-__device__ __forceinline__ void st4(lds_v2* p, float a, float b, float c, float d) {
-  *reinterpret_cast<lds_v4*>(p) = v4f{a, b, c, d};
-}
 
 template <int CTRL>
 static __device__ __forceinline__ float2 dpp2(float2 v) { return f2(dppf<CTRL>(v.x), dppf<CTRL>(v.y)); }
@@ -84,12 +65,6 @@ static __device__ __forceinline__ float2 dpp2(float2 v) { return f2(dppf<CTRL>(v
 // value held by lane (r, -ky mod 16) of the same row: the row mirrored
 // (lane j gets 15 - j), then rotated by one
 static __device__ __forceinline__ float2 row_neg(float2 v) { return dpp2<ROR1>(dpp2<MIRROR>(v)); }
-
-static __device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // Observer state of the 16x16x8 kernel, per pixel: [kz / 2][plane][ky] x
 // (kz even, kz odd) complex, so that one 16-byte load per lane covers 1 KB

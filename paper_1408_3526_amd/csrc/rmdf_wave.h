@@ -8,6 +8,34 @@
 
 namespace rmdf {
 
+// LDS pointers keep their address space so every access is a ds_* instruction
+// with an immediate offset (a generic pointer would become a flat access)
+#define RMDF_LDS __attribute__((address_space(3)))
+#define RMDF_GLOBAL __attribute__((address_space(1)))
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef RMDF_LDS v2f lds_v2;
+typedef RMDF_LDS v4f lds_v4;
+typedef RMDF_LDS float lds_float;
+__device__ __forceinline__ float2 ld2(const lds_v2* p) { const v2f v = *p; return make_float2(v.x, v.y); }
+__device__ __forceinline__ float4 ld4(const lds_v2* p) {
+  const v4f v = *reinterpret_cast<const lds_v4*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st2(lds_v2* p, float2 v) { *p = v2f{v.x, v.y}; }
+__device__ __forceinline__ void st4(lds_v2* p, float a, float b, float c, float d) {
+  *reinterpret_cast<lds_v4*>(p) = v4f{a, b, c, d};
+}
+
+// Orders this wavefront's LDS accesses (lanes of one wavefront exchange
+// through LDS without a workgroup barrier).
+static __device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <int CTRL>
 static __device__ __forceinline__ float dppf(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
