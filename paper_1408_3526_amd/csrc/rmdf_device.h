@@ -22,17 +22,6 @@ static __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 static __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 static __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 
-// Element at a byte offset from a base that is the same in all lanes: a 32-bit
-// offset per lane instead of a 64-bit address.
-template <class T>
-static __device__ __forceinline__ const T& at(const T* base, unsigned bytes) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
-}
-template <class T>
-static __device__ __forceinline__ T& at(T* base, unsigned bytes) {
-  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
-}
-
 // A column of N complex values in LDS at a 16-byte aligned address: 16-byte
 // accesses, the last value of an odd N alone.
 template <int N>

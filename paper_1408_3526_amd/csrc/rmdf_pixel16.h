@@ -8,16 +8,29 @@
 // complex observer states.  Per row:
 //   column sliding DFT        in registers (one resonator per column)
 //   deadbeat observer         in registers; state streamed once (8 KB/pixel
-//                             read + 8 KB written, prefetched one row ahead)
+//                             read + 8 KB written)
 //   high-pass, Hann along kz  in registers
 //   Hann along ky             DPP row rotations (a row of 16 lanes = one plane)
-//   unpack of kx = 0 / 8      DPP row mirror (the -ky partner) + register (-kz)
-//   Hann along kx, P, stage A LDS exchange of neighbouring planes
-//   stage B (ky -> l_y)       lanes = (kx group, l_y); even/odd split in ky
-//   stage C (kx -> l_x)       lanes = (l_y group, l_x); smoothing; argmax
+//   unpack of kx = 0 / 8      from LDS, one kz pair per lane
+//   Hann along kx, P, stage A LDS exchange of neighbouring planes: planes 1-4
+//                             and 5-8 in two full passes, plane 0 spread over
+//                             all lanes
+//   stage B (ky -> l_y)       lanes = (kx, l_y mod 7); even/odd split in ky
+//   stage C (kx -> l_x)       lanes = (l_y group, l_x pair); smoothing; argmax
 //   background estimate       lanes' own columns x coefficient table
 // Trigonometric weights of stages B and C are staged in LDS once per tile
 // and read into registers for each row's stage.
+//
+// What bounds it (640x512, 17x17 candidates): one observer frame its HBM bytes
+// (1.16 ms a frame, 5.2 TB/s); the forms that move half of them (frame pairs,
+// the ring) the VALU, 1 050 instructions an anchor and frame, 85% busy in the
+// ring.  So those forms run three wavefronts per SIMD (at most 168 registers,
+// 50.7 KB of LDS per workgroup) and leave latency to the other wavefronts, and
+// the modes that stream a whole observer state run two with the next row's state
+// loaded one row ahead (three without: 1.20 against 1.18 ms).  Against two
+// wavefronts with the prefetch throughout, four passes along kx and one candidate
+// per T read in stage C: ring 1.10 -> 0.84 ms, pairs 1.06 -> 0.89 ms a frame,
+// refined 317x243 0.336 -> 0.297 ms, single frames 1.23 -> 1.17 ms.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -34,11 +47,15 @@ constexpr int MX = 16, MY = 16, MZ = 8;
 constexpr int NXH = 9;            // kx = 0..8
 constexpr int NCOL = 128;         // 8 planes x 16 ky
 constexpr int WAVES = 4;          // anchors (x) per workgroup
-constexpr int SB_PLANES = 9;      // kx = 0 .. 8
-constexpr int SB_KZ = 10;         // kz slots per (plane, ky) row: 80 B, so a row of 16
-                                  // lanes writing 16 B each covers 64 distinct banks
-constexpr int SB_ELEMS = SB_PLANES * MY * SB_KZ;   // float2 per wave
+constexpr int SB_PLANES = 10;     // kx = 0 .. 9 (9: the conjugate mirror of 7)
+constexpr int SB_PLANE = MY * MZ; // float2 per plane: rows of 64 B, see sb_pair
+constexpr int SB_ELEMS = SB_PLANES * SB_PLANE;     // float2 per wave
 constexpr int NV1_MAX = 21;       // 3 lane groups x 21 <= 64
+constexpr int TABW = 20;          // floats per weight row of stages B and C in LDS (16 used; 80 B
+                                  // rows of neighbouring lanes fall on distinct banks)
+constexpr int GROW = 10;          // float2 per row of the lattice table in LDS (8 used; as TABW)
+constexpr int TROW = 10;          // float2 per T row (one l_y, kx = 0 .. 8; as TABW)
+constexpr int LB = 7;             // stage B lanes per kx
 
 static __device__ __forceinline__ float2 f2(float x, float y) { return make_float2(x, y); }
 
@@ -66,6 +83,11 @@ static __device__ __forceinline__ float2 dpp2(float2 v) { return f2(dppf<CTRL>(v
 // (lane j gets 15 - j), then rotated by one
 static __device__ __forceinline__ float2 row_neg(float2 v) { return dpp2<ROR1>(dpp2<MIRROR>(v)); }
 
+// The value is computed here, and memory accesses are not moved across (no
+// instruction): without it the compiler sinks a pass's arithmetic below the next
+// pass's loads and holds both in registers.
+static __device__ __forceinline__ void pass_done(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory"); }
+
 // Observer state of the 16x16x8 kernel, per pixel: [kz / 2][plane][ky] x
 // (kz even, kz odd) complex, so that one 16-byte load per lane covers 1 KB
 // of contiguous memory across the wavefront.  Float2 index of (plane, ky, kz):
@@ -73,8 +95,10 @@ static __host__ __device__ __forceinline__ int st16_index(int p, int ky, int kz)
   return ((kz >> 1) * NCOL + p * MY + ky) * 2 + (kz & 1);
 }
 
-// s_b index of (plane kx in [0, 8], ky, kz)
-static __device__ __forceinline__ int sb_idx(int kx, int ky, int kz) { return (kx * MY + ky) * SB_KZ + kz; }
+// Staged planes in LDS: index within a plane of the kz pair (2j, 2j + 1) of row
+// ky.  The four 16-byte pairs of a row are rotated by ky / 4, so that a row of
+// 16 lanes accessing one pair each covers all 64 banks.
+static __device__ __forceinline__ int sb_pair(int ky, int j) { return ky * MZ + (((j + (ky >> 2)) & 3) << 1); }
 
 // w_8^k X for the eight posterior states (exact rotations for even k)
 static __device__ __forceinline__ float2 rot8(float2 a, int k) {
@@ -103,8 +127,8 @@ static __device__ __forceinline__ float2 stageA(const float P[MZ]) {
 constexpr int LATQ_MAX = 64;      // rows of the lattice coefficient table
 constexpr int NC_IT = (NV1_MAX + 2) / 3;   // stage-C iterations per lane
 constexpr int ETAB = 8 * 17;        // spatial factors [kx 0..7][ky -8..8], zero outside the band
-constexpr size_t SMEM16 = sizeof(float2) * WAVES * SB_ELEMS + sizeof(float4) * 2 * NV1_MAX * 4 +
-                          sizeof(float2) * (LATQ_MAX * MZ + ETAB);
+constexpr size_t SMEM16 = sizeof(float2) * WAVES * SB_ELEMS + sizeof(float) * 2 * NV1_MAX * TABW +
+                          sizeof(float2) * (LATQ_MAX * GROW + ETAB + 2 * ((NV1_MAX + 1) / 2));
 // mode 5 (direct column DFT): per wavefront, the row spectra of the last My
 // rows ([row mod 16][r] x (plane r, plane r + 4)), and the table w_y^k
 constexpr int CRING = MY * 4;             // float4 per wavefront
@@ -112,37 +136,54 @@ constexpr size_t SMEM16_DIRECT = SMEM16 + sizeof(float4) * WAVES * CRING + sizeo
 template <int MODE>
 constexpr size_t smem16_bytes() { return MODE == 5 ? SMEM16_DIRECT : SMEM16; }
 
-// Hann along kx, power spectrum and stage A for one (plane kx, ky) column
-// of kz values.  The centre comes from registers (CREG) or from LDS; the
-// neighbours from LDS.  Plane -1 is the conjugate mirror of plane 1 and
-// plane 9 that of plane 7: S(-1, ky, kz) = conj S(1, -ky, -kz),
-// S(9, ky, kz) = conj S(7, -ky, -kz).  EDGE: 0 interior, 1 kx = 0, 2 kx = 8.
-template <int EDGE, bool CREG>
-static __device__ __forceinline__ float2 hann_x_power(const lds_v2* s_b, int ky, int kx, const float2 (&Hc)[MZ],
-                                                      float (&P)[MZ]) {
+// One (ky) row of a staged plane, all kz; rp[j] = sb_pair(row, j).
+static __device__ __forceinline__ void ld_row(const lds_v2* plane, const int (&rp)[MZ / 2], float2 (&v)[MZ]) {
 #pragma unroll
-  for (int k = 0; k < MZ; k += 2) {
-    float4 l, rr, cc;
-    if (EDGE == 1) {
-      const float2 m0 = ld2(&s_b[sb_idx(1, (MY - ky) & 15, (MZ - k) & 7)]);
-      const float2 m1 = ld2(&s_b[sb_idx(1, (MY - ky) & 15, (MZ - k - 1) & 7)]);
-      l = make_float4(m0.x, -m0.y, m1.x, -m1.y);
-    } else {
-      l = ld4(&s_b[sb_idx(kx - 1, ky, k)]);
+  for (int j = 0; j < MZ / 2; ++j) {
+    const float4 q = ld4(plane + rp[j]);
+    v[2 * j] = f2(q.x, q.y);
+    v[2 * j + 1] = f2(q.z, q.w);
+  }
+}
+
+// conj of a row with kz negated: the row of plane -kx at -ky
+static __device__ __forceinline__ void conj_neg(float2 (&v)[MZ]) {
+  float2 t[MZ];
+#pragma unroll
+  for (int k = 0; k < MZ; ++k) t[k] = f2(v[(MZ - k) & 7].x, -v[(MZ - k) & 7].y);
+#pragma unroll
+  for (int k = 0; k < MZ; ++k) v[k] = t[k];
+}
+
+// Hann along kx and power for one kz: |2 c - l - r|^2 (l subtracted first)
+static __device__ __forceinline__ float hann_pow(float2 c, float2 l, float2 r) {
+  const float hx = 2.f * c.x - l.x - r.x, hy = 2.f * c.y - l.y - r.y;
+  return hx * hx + hy * hy;
+}
+
+// Hann along kx, power spectrum and stage A for one (plane kx, ky) column of
+// kz values; c, l, r: the planes kx, kx - 1, kx + 1.  LM / RM: that neighbour
+// is the conjugate mirror of the plane given (rows of -ky in mp):
+// S(-1, ky, kz) = conj S(1, -ky, -kz), S(9, ky, kz) = conj S(7, -ky, -kz).
+template <bool LM, bool RM>
+static __device__ __forceinline__ float2 hann_x_power(const lds_v2* c, const lds_v2* l, const lds_v2* r,
+                                                      const int (&rp)[MZ / 2], const int (&mp)[MZ / 2], float (&P)[MZ]) {
+  if (LM || RM) {
+    float2 vl[MZ], vr[MZ], vc[MZ];
+    ld_row(l, LM ? mp : rp, vl);
+    if (LM) conj_neg(vl);
+    ld_row(r, RM ? mp : rp, vr);
+    if (RM) conj_neg(vr);
+    ld_row(c, rp, vc);
+#pragma unroll
+    for (int k = 0; k < MZ; ++k) P[k] = hann_pow(vc[k], vl[k], vr[k]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < MZ / 2; ++j) {
+      const float4 vl = ld4(l + rp[j]), vr = ld4(r + rp[j]), vc = ld4(c + rp[j]);
+      P[2 * j] = hann_pow(f2(vc.x, vc.y), f2(vl.x, vl.y), f2(vr.x, vr.y));
+      P[2 * j + 1] = hann_pow(f2(vc.z, vc.w), f2(vl.z, vl.w), f2(vr.z, vr.w));
     }
-    if (EDGE == 2) {
-      const float2 m0 = ld2(&s_b[sb_idx(7, (MY - ky) & 15, (MZ - k) & 7)]);
-      const float2 m1 = ld2(&s_b[sb_idx(7, (MY - ky) & 15, (MZ - k - 1) & 7)]);
-      rr = make_float4(m0.x, -m0.y, m1.x, -m1.y);
-    } else {
-      rr = ld4(&s_b[sb_idx(kx + 1, ky, k)]);
-    }
-    if (CREG) cc = make_float4(Hc[k].x, Hc[k].y, Hc[k + 1].x, Hc[k + 1].y);
-    else cc = ld4(&s_b[sb_idx(kx, ky, k)]);
-    const float h0x = 2.f * cc.x - l.x - rr.x, h0y = 2.f * cc.y - l.y - rr.y;
-    const float h1x = 2.f * cc.z - l.z - rr.z, h1y = 2.f * cc.w - l.w - rr.w;
-    P[k] = h0x * h0x + h0y * h0y;
-    P[k + 1] = h1x * h1x + h1y * h1y;
   }
   return stageA(P);
 }
@@ -247,31 +288,34 @@ static __device__ __forceinline__ void dft8p_scaled(const float2* x, float2* X) 
 template <int MODE>
 static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const float* ring_delayed, int xb, int yb, char* smem) {
   lds_v2* s_all = (lds_v2*)(smem);
-  lds_v4* s_tab = (lds_v4*)(smem + sizeof(float2) * WAVES * SB_ELEMS);  // tabB rows, then tabC rows
-  lds_v2* s_g = (lds_v2*)(smem + sizeof(float2) * WAVES * SB_ELEMS + sizeof(float4) * 2 * NV1_MAX * 4);
+  lds_float* s_tabB = (lds_float*)(smem + sizeof(float2) * WAVES * SB_ELEMS);   // [nvy][TABW]
+  lds_float* s_tabC = s_tabB + NV1_MAX * TABW;                                  // [nvx][TABW]
+  lds_v2* s_g = (lds_v2*)(s_tabC + NV1_MAX * TABW);                             // [lat_q][GROW], then E
+  lds_float* s_gx = (lds_float*)(s_g + LATQ_MAX * GROW + ETAB);                 // [nvx], then gy [nvy]
   const int lane = threadIdx.x & 63;
   // wave-uniform values live in scalar registers
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   lds_v2* s_b = s_all + wv * SB_ELEMS;
   lds_v2* s_q = s_b;                       // [9][16] after Hann along kx
-  lds_v2* s_t = s_b + NXH * MY;            // [9][NV1_MAX]
+  lds_v2* s_t = s_b + NXH * MY;            // [nvy][TROW]
+  lds_v2* s_p = s_t + NV1_MAX * TROW;      // [16][4]: P of plane 0, kz pairs
   const int nvx = a.nvx, nvy = a.nvy, nv = a.nv;
   {
-    const float4* tb = reinterpret_cast<const float4*>(a.tabB);
-    const float4* tc = reinterpret_cast<const float4*>(a.tabC);
-    for (int i = threadIdx.x; i < 4 * nvy; i += 256) s_tab[i] = v4f{tb[i].x, tb[i].y, tb[i].z, tb[i].w};
-    for (int i = threadIdx.x; i < 4 * nvx; i += 256) s_tab[4 * NV1_MAX + i] = v4f{tc[i].x, tc[i].y, tc[i].z, tc[i].w};
+    for (int i = threadIdx.x; i < nvx + nvy; i += 256) s_gx[i] = (i < nvx) ? a.gx[i] : a.gy[i - nvx];
+    for (int i = threadIdx.x; i < 16 * nvy; i += 256) s_tabB[(i >> 4) * TABW + (i & 15)] = a.tabB[i];
+    for (int i = threadIdx.x; i < 16 * nvx; i += 256) s_tabC[(i >> 4) * TABW + (i & 15)] = a.tabC[i];
     if (MODE == 5 && threadIdx.x < MY) {
       lds_v2* wy_tab = (lds_v2*)(smem + SMEM16 + sizeof(float4) * WAVES * CRING);
       wy_tab[threadIdx.x] = v2f{a.twy[threadIdx.x].x, a.twy[threadIdx.x].y};
     }
     if (a.gtab != nullptr) {
-      for (int i = threadIdx.x; i < a.lat_q * MZ; i += 256) s_g[i] = v2f{a.gtab[i].x, a.gtab[i].y};
+      for (int i = threadIdx.x; i < a.lat_q * MZ; i += 256)
+        s_g[(i >> 3) * GROW + (i & 7)] = v2f{a.gtab[i].x, a.gtab[i].y};
       for (int i = threadIdx.x; i < ETAB; i += 256) {
         const int p = i / 17, kc = i % 17 - 8;
         float2 e = f2(0.f, 0.f);
         if (p <= a.bx && kc >= -a.by && kc <= a.by) e = a.etab[p * (2 * a.by + 1) + kc + a.by];
-        s_g[LATQ_MAX * MZ + i] = v2f{e.x, e.y};
+        s_g[LATQ_MAX * GROW + i] = v2f{e.x, e.y};
       }
     }
   }
@@ -285,11 +329,28 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
 
   const int r = lane >> 4, ky = lane & 15;
   const int pA = r, pB = r + 4;
-  // stage B lane (g, iy), stage C lane (h, ix)
-  const int gB = lane / nvy, iyB = lane % nvy;
-  const bool actB = lane < 3 * nvy;
-  const int hC = lane / nvx, ixC = lane % nvx;
-  const bool actC = lane < 3 * nvx;
+  // staging rows: this lane's ky and its mirror -ky; pair r of each for the
+  // steps that spread a plane's four kz pairs over the four lane groups
+  const int my = (MY - ky) & 15;
+  int rp[MZ / 2], mp[MZ / 2];
+#pragma unroll
+  for (int j = 0; j < MZ / 2; ++j) {
+    rp[j] = sb_pair(ky, j);
+    mp[j] = sb_pair(my, j);
+  }
+  const int oj = sb_pair(ky, r);                                   // kz = 2r, 2r + 1
+  const int m0 = sb_pair(my, (4 - r) & 3), m1 = sb_pair(my, 3 - r) + 1;   // row -ky, kz = -2r, -2r - 1
+  // stage B: LB lanes per kx, lane g taking l_y = g, g + LB, ...
+  const int kxB = lane / LB, gB = lane - kxB * LB;
+  // stage C: a lane takes KX = 2 candidates of one l_y (ix and ix + LC), or
+  // one where that needs fewer rounds (nvx > 18); GC l_y at a time
+  const bool two = nvx <= 18;
+  const int LC = two ? (nvx + 1) >> 1 : nvx;
+  const int GC = two ? min(64 / LC, NV1_MAX) : 3;
+  const int hC = lane / LC, ixC = lane - hC * LC;
+  const bool onC = hC < GC, second = ixC + LC < nvx;
+  const int wC0 = hC * nvx + ixC;          // first candidate; GC nvx further on each round
+  const int magic_nvx = (65536 + nvx - 1) / nvx;   // istar / nvx = istar magic >> 16 (istar < 441)
   const float2 wy = a.twy[ky];
   const int kyc = (ky <= 8) ? ky : ky - 16;
   // lattice background coefficients (table and spatial factors in LDS)
@@ -297,8 +358,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
 
   // row spectra [y][x][plane]: element (row yy) at rsA[yy * rstride]
   const size_t rstride = (size_t)a.W * 8;
-  const float2* rsA = a.rs + (size_t)x * 8 + pA;
-  const float2* rsB = a.rs + (size_t)x * 8 + pB;
+  const float2* rs1 = a.rs + (size_t)x * 8;        // (the same in all lanes)
+  const unsigned roA = 8u * pA, roB = 8u * pB;
 
   // column sliding DFT seeded with the 16 rows above the tile (Horner form of
   // the direct DFT: the same resonator run over those rows; rows above the
@@ -306,6 +367,7 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
   // start costs one memory latency.
   float2 acA = f2(0.f, 0.f), acB = f2(0.f, 0.f);
   constexpr bool RING = (MODE == 4 || MODE == 5);
+  constexpr bool PREFETCH = (MODE <= 2);
   // mode 5: row spectra of the last My rows of this column, slot = row mod 16
   lds_v4* s_cr = (lds_v4*)(smem + SMEM16) + wv * CRING;
   const lds_v2* s_wy = (const lds_v2*)(smem + SMEM16 + sizeof(float4) * WAVES * CRING);
@@ -314,8 +376,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
 #pragma unroll
     for (int i = 0; i < MY; ++i) {
       const int yy = y0 - MY + i;
-      sA[i] = (yy >= 0) ? rsA[(size_t)yy * rstride] : f2(0.f, 0.f);
-      sB[i] = (yy >= 0) ? rsB[(size_t)yy * rstride] : f2(0.f, 0.f);
+      sA[i] = (yy >= 0) ? at(rs1 + (size_t)yy * rstride, roA) : f2(0.f, 0.f);
+      sB[i] = (yy >= 0) ? at(rs1 + (size_t)yy * rstride, roB) : f2(0.f, 0.f);
     }
     if (MODE == 5) {
       if (ky == 0) {
@@ -333,15 +395,14 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
 
   // mode 6: the pair's second frame has its own row spectra and column SDFT
   float2 acA2 = f2(0.f, 0.f), acB2 = f2(0.f, 0.f);
-  const float2* rsA2 = (MODE == 6) ? a.rs2 + (size_t)x * 8 + pA : rsA;
-  const float2* rsB2 = (MODE == 6) ? a.rs2 + (size_t)x * 8 + pB : rsB;
+  const float2* rs2 = (MODE == 6) ? a.rs2 + (size_t)x * 8 : rs1;
   if (MODE == 6) {
     float2 sA[MY], sB[MY];
 #pragma unroll
     for (int i = 0; i < MY; ++i) {
       const int yy = y0 - MY + i;
-      sA[i] = (yy >= 0) ? rsA2[(size_t)yy * rstride] : f2(0.f, 0.f);
-      sB[i] = (yy >= 0) ? rsB2[(size_t)yy * rstride] : f2(0.f, 0.f);
+      sA[i] = (yy >= 0) ? at(rs2 + (size_t)yy * rstride, roA) : f2(0.f, 0.f);
+      sB[i] = (yy >= 0) ? at(rs2 + (size_t)yy * rstride, roB) : f2(0.f, 0.f);
     }
 #pragma unroll
     for (int i = 0; i < MY; ++i) {
@@ -350,9 +411,9 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
     }
   }
 
-  // Rows are software-pipelined: the observer state and row-spectrum samples
-  // of row y + 1 are loaded as soon as row y has staged its planes in LDS, so
-  // their HBM latency hides behind the flow stages of row y.  State layout:
+  // PREFETCH: rows are software-pipelined, the observer state and row-spectrum
+  // samples of row y + 1 loaded as soon as row y has staged its planes in LDS,
+  // so their HBM latency hides behind the flow stages of row y.  State layout:
   // [kz pair][plane][ky] x 2 complex per pixel (st16_index), one 1 KB
   // contiguous run per instruction.
   float4 SnA[MZ / 2], SnB[MZ / 2];
@@ -360,42 +421,50 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
   const int slot0 = __builtin_amdgcn_readfirstlane(a.tcur & 7);   // mode 4: slot of the new frame
   float2 nA, nB, oA = f2(0.f, 0.f), oB = f2(0.f, 0.f);   // rs(y), rs(y - My)
   float2 nA2 = f2(0.f, 0.f), nB2 = f2(0.f, 0.f), oA2 = f2(0.f, 0.f), oB2 = f2(0.f, 0.f);   // mode 6
-  {
+  auto load_state = [&](int y) {
+    const size_t pix = (size_t)y * a.W + x;
     if (RING) {
-      const float2* src = a.st + ((size_t)y0 * a.W + x) * NCOL * MZ;
+      const float2* src = a.st + pix * NCOL * MZ;
 #pragma unroll
       for (int m = 1; m < MZ; ++m) {
         const int s = (slot0 - m) & 7;
-        RA[m] = ld2_stream(&src[s * NCOL + pA * MY + ky]);
-        RB[m] = ld2_stream(&src[s * NCOL + pB * MY + ky]);
+        RA[m] = ld2_stream(&at(src + s * NCOL, 8u * lane));
+        RB[m] = ld2_stream(&at(src + s * NCOL + NCOL / 2, 8u * lane));
       }
     } else {
-      const float4* src = reinterpret_cast<const float4*>(a.st + ((size_t)y0 * a.W + x) * NCOL * MZ);
+      const float4* src = reinterpret_cast<const float4*>(a.st + pix * NCOL * MZ);
 #pragma unroll
       for (int j = 0; j < MZ / 2; ++j) {
-        SnA[j] = ld_stream(&src[j * NCOL + pA * MY + ky]);
-        SnB[j] = ld_stream(&src[j * NCOL + pB * MY + ky]);
+        SnA[j] = ld_stream(&at(src + j * NCOL, 16u * lane));
+        SnB[j] = ld_stream(&at(src + j * NCOL + NCOL / 2, 16u * lane));
       }
     }
-    nA = rsA[(size_t)y0 * rstride];
-    nB = rsB[(size_t)y0 * rstride];
-    if (MODE != 5 && y0 >= MY) {
-      oA = rsA[(size_t)(y0 - MY) * rstride];
-      oB = rsB[(size_t)(y0 - MY) * rstride];
+  };
+  auto load_rows = [&](int y, const float2* rs, float2& na, float2& nb, float2& oa, float2& ob) {
+    na = at(rs + (size_t)y * rstride, roA);
+    nb = at(rs + (size_t)y * rstride, roB);
+    if (MODE != 5 && y >= MY) {
+      oa = at(rs + (size_t)(y - MY) * rstride, roA);
+      ob = at(rs + (size_t)(y - MY) * rstride, roB);
     }
-    if (MODE == 6) {
-      nA2 = rsA2[(size_t)y0 * rstride];
-      nB2 = rsB2[(size_t)y0 * rstride];
-      if (y0 >= MY) {
-        oA2 = rsA2[(size_t)(y0 - MY) * rstride];
-        oB2 = rsB2[(size_t)(y0 - MY) * rstride];
-      }
-    }
+  };
+  if (PREFETCH) {
+    load_state(y0);
+    load_rows(y0, rs1, nA, nB, oA, oB);
   }
 
   for (int y = y0; y < y1; ++y) {
     const size_t pix = (size_t)y * a.W + x;
+    float* rq = a.rsm + pix * nv;
+    // opaque per row: what stage C derives from the lane's place is computed
+    // again each row instead of being held in registers across the loop
+    int wC = wC0;
+    asm volatile("" : "+v"(wC));
     float2 XA[MZ], XB[MZ];
+    if (!PREFETCH) {
+      load_rows(y, rs1, nA, nB, oA, oB);
+      load_state(y);
+    }
     if (!RING) {
 #pragma unroll
       for (int j = 0; j < MZ / 2; ++j) {
@@ -419,8 +488,6 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       float2& cnB = F ? nB2 : nB;
       float2& coA = F ? oA2 : oA;
       float2& coB = F ? oB2 : oB;
-      const float2* frA = F ? rsA2 : rsA;
-      const float2* frB = F ? rsB2 : rsB;
       const float* rdel = F ? a.ring_delayed2 : ring_delayed;
       if (MODE == 5) {
         // ---- column DFT, direct: sum_m w_y^(ky m) rs(y - m), m = 0 .. 15
@@ -450,8 +517,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
         dft8p_scaled(RA, XA);
         dft8p_scaled(RB, XB);
         float2* dst = a.st + pix * NCOL * MZ + slot0 * NCOL;
-        st2_stream(&dst[pA * MY + ky], RA[0]);
-        st2_stream(&dst[pB * MY + ky], RB[0]);
+        st2_stream(&at(dst, 8u * lane), RA[0]);
+        st2_stream(&at(dst + NCOL / 2, 8u * lane), RB[0]);
       } else {
         // ---- deadbeat observer (posterior rotated, innovation shared by all kz)
         float2 sA = f2(0.f, 0.f), sB2 = f2(0.f, 0.f);
@@ -473,8 +540,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
         float4* dst = reinterpret_cast<float4*>(a.st + pix * NCOL * MZ);
 #pragma unroll
         for (int j = 0; j < (LAST ? MZ / 2 : 0); ++j) {
-          st_stream(&dst[j * NCOL + pA * MY + ky], XA[2 * j].x, XA[2 * j].y, XA[2 * j + 1].x, XA[2 * j + 1].y);
-          st_stream(&dst[j * NCOL + pB * MY + ky], XB[2 * j].x, XB[2 * j].y, XB[2 * j + 1].x, XB[2 * j + 1].y);
+          st_stream(&at(dst + j * NCOL, 16u * lane), XA[2 * j].x, XA[2 * j].y, XA[2 * j + 1].x, XA[2 * j + 1].y);
+          st_stream(&at(dst + j * NCOL + NCOL / 2, 16u * lane), XB[2 * j].x, XB[2 * j].y, XB[2 * j + 1].x, XB[2 * j + 1].y);
         }
       }
       // ---- high-pass + Hann along kz (2X(k) - X(k-1) - X(k+1); the 1/4 per
@@ -483,11 +550,14 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       {
         float2 V[MZ];
         const bool dc = (lane == 0);       // plane 0 (kx = 0 | kx = 8 packed), ky = 0
+        // drop the kx = 0 part: C - (C + conj C(-kz)) / 2 (odd in kz along x, even
+        // along y: half of the kz are computed)
 #pragma unroll
-        for (int k = 0; k < MZ; ++k) {
+        for (int k = 0; k <= MZ / 2; ++k) {
           const float2 m = XA[(MZ - k) & 7];
-          // drop the kx = 0 part: C - (C + conj C(-kz)) / 2
-          V[k] = dc ? f2(0.5f * (XA[k].x - m.x), 0.5f * (XA[k].y + m.y)) : XA[k];
+          const float hx = 0.5f * (XA[k].x - m.x), hy = 0.5f * (XA[k].y + m.y);
+          V[k] = f2(dc ? hx : XA[k].x, dc ? hy : XA[k].y);
+          if (k > 0 && k < MZ / 2) V[MZ - k] = f2(dc ? -hx : m.x, dc ? hy : m.y);
         }
 #pragma unroll
         for (int k = 0; k < MZ; ++k) {
@@ -509,37 +579,44 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       // S(0) = (C + conj C(-k)) / 2, S(8) = (C - conj C(-k)) / 2j
       wave_lds_sync();                     // previous row's stage C reads are done
 #pragma unroll
-      for (int k = 0; k < MZ; k += 2) {
-        st4(&s_b[sb_idx(pA, ky, k)], HA[k].x, HA[k].y, HA[k + 1].x, HA[k + 1].y);
-        st4(&s_b[sb_idx(pB, ky, k)], HB[k].x, HB[k].y, HB[k + 1].x, HB[k + 1].y);
+      for (int j = 0; j < MZ / 2; ++j) {
+        st4(s_b + pA * SB_PLANE + rp[j], HA[2 * j].x, HA[2 * j].y, HA[2 * j + 1].x, HA[2 * j + 1].y);
+        st4(s_b + pB * SB_PLANE + rp[j], HB[2 * j].x, HB[2 * j].y, HB[2 * j + 1].x, HB[2 * j + 1].y);
       }
-      wave_lds_sync();
-      if (r == 0) {
-        // every read of plane 0 precedes every write to it (one wavefront,
-        // program order)
-        float2 w[MZ];
+      if (MODE != 1 && MODE != 2 && r == 3) {
+        // plane 9 = conj of plane 7 at (-ky, -kz)
 #pragma unroll
-        for (int k = 0; k < MZ; ++k) w[k] = ld2(&s_b[sb_idx(0, (MY - ky) & 15, (MZ - k) & 7)]);
-#pragma unroll
-        for (int k = 0; k < MZ; k += 2) {
-          const float2 u0 = HA[k], u1 = HA[k + 1], w0 = w[k], w1 = w[k + 1];
-          st4(&s_b[sb_idx(8, ky, k)], 0.5f * (u0.y + w0.y), -0.5f * (u0.x - w0.x), 0.5f * (u1.y + w1.y),
-              -0.5f * (u1.x - w1.x));
-          st4(&s_b[sb_idx(0, ky, k)], 0.5f * (u0.x + w0.x), 0.5f * (u0.y - w0.y), 0.5f * (u1.x + w1.x),
-              0.5f * (u1.y - w1.y));
+        for (int j = 0; j < MZ / 2; ++j) {
+          const float2 h0 = HB[(MZ - 2 * j) & 7], h1 = HB[MZ - 1 - 2 * j];
+          st4(s_b + 9 * SB_PLANE + mp[j], h0.x, -h0.y, h1.x, -h1.y);
         }
       }
       wave_lds_sync();
+      {
+        // each lane unpacks one kz pair; every read of plane 0 precedes every
+        // write to it (one wavefront, program order)
+        const float4 u = ld4(s_b + oj);
+        const float2 w0 = ld2(s_b + m0), w1 = ld2(s_b + m1);
+        wave_lds_sync();
+        st4(s_b + 8 * SB_PLANE + oj, 0.5f * (u.y + w0.y), -0.5f * (u.x - w0.x), 0.5f * (u.w + w1.y),
+            -0.5f * (u.z - w1.x));
+        st4(s_b + oj, 0.5f * (u.x + w0.x), 0.5f * (u.y - w0.y), 0.5f * (u.z + w1.x), 0.5f * (u.w - w1.y));
+      }
+      wave_lds_sync();
       // issued here so that their latency overlaps the rest of the flow: this
-      // row's smoothed autocorrelation (stage-C lane (hC, ixC) owns the
-      // candidates iy = hC + 3j; rows past the grid read the last one) and the
-      // delayed input sample
+      // row's smoothed autocorrelation (the candidates of the lane's place in
+      // stage C; places past the grid read its last value) and the delayed
+      // input sample
       float idel = 0.f;
       if (MODE != 2 && F == 0) {
-        const float* rp = a.rsm + pix * nv;
-        const int off0 = hC * nvx + ixC, offl = (nvy - 1) * nvx + ixC;
+        if (two) {
 #pragma unroll
-        for (int j = 0; j < NC_IT; ++j) rprev[j] = rp[(unsigned)min(off0 + 3 * j * nvx, offl)];
+          for (int j = 0; j < NC_IT - 1; ++j)
+            rprev[j] = at(rq, 4u * (unsigned)min(wC + ((j >> 1) * GC * nvx + (j & 1) * LC), nv - 1));
+        } else {
+#pragma unroll
+          for (int j = 0; j < NC_IT; ++j) rprev[j] = at(rq, 4u * (unsigned)min(wC + 3 * j * nvx, nv - 1));
+        }
       }
       {
         const int xs = x - a.dx, ys = y - a.dy;
@@ -548,46 +625,53 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       // next row's state and row-spectrum samples (see the pipeline note);
       // issued after the loads above, which stage C waits for (vector memory
       // completes in order)
-      if (y + 1 < y1) {
-        if (F > 0) {
-        } else if (RING) {
-          const float2* src = a.st + (pix + a.W) * NCOL * MZ;
-#pragma unroll
-          for (int m = 1; m < MZ; ++m) {
-            const int s = (slot0 - m) & 7;
-            RA[m] = ld2_stream(&src[s * NCOL + pA * MY + ky]);
-            RB[m] = ld2_stream(&src[s * NCOL + pB * MY + ky]);
-          }
-        } else {
-          const float4* src = reinterpret_cast<const float4*>(a.st + (pix + a.W) * NCOL * MZ);
-#pragma unroll
-          for (int j = 0; j < MZ / 2; ++j) {
-            SnA[j] = ld_stream(&src[j * NCOL + pA * MY + ky]);
-            SnB[j] = ld_stream(&src[j * NCOL + pB * MY + ky]);
-          }
-        }
-        cnA = frA[(size_t)(y + 1) * rstride];
-        cnB = frB[(size_t)(y + 1) * rstride];
-        if (MODE != 5 && y + 1 >= MY) {
-          coA = frA[(size_t)(y + 1 - MY) * rstride];
-          coB = frB[(size_t)(y + 1 - MY) * rstride];
-        }
+      if (MODE == 6 && F == 0) load_rows(y, rs2, nA2, nB2, oA2, oB2);
+      if (PREFETCH && y + 1 < y1) {
+        if (F == 0) load_state(y + 1);
+        load_rows(y + 1, F ? rs2 : rs1, cnA, cnB, coA, coB);
       }
 
       // ---- Hann along kx, power spectrum, stage A: Q(kx, ky) = sum_kz P w_z^kz.
       // Planes -1 and 9 are the conjugate mirrors of planes 1 and 7:
       // S(-1, ky, kz) = conj S(1, -ky, -kz), S(9, ky, kz) = conj S(7, -ky, -kz).
-      float2 QA, QB, Q8 = f2(0.f, 0.f);
+      // Planes r + 1 and r + 5 in two full passes, plane 0 spread over all lanes
+      // (one kz pair each).  The modes that write features keep the lane to plane
+      // assignment r, r + 4 (and 8 on r = 0) that their sums run over.
+      constexpr bool FEAT = (MODE == 1 || MODE == 2);
+      constexpr int KA = FEAT ? 0 : 1;
+      float2 QA, QB, QX = f2(0.f, 0.f);    // planes r + KA, r + 4 + KA; QX: plane 8 (FEAT) or 0 on r = 0
       float PA[MZ], PB[MZ], P8[MZ];
+      if (FEAT) {
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) P8[k] = 0.f;
-      if (r == 0) {
-        QA = hann_x_power<1, false>(s_b, ky, 0, HA, PA);
-        Q8 = hann_x_power<2, false>(s_b, ky, 8, HA, P8);
+        for (int k = 0; k < MZ; ++k) P8[k] = 0.f;
+        if (r == 0) {
+          QA = hann_x_power<true, false>(s_b, s_b + SB_PLANE, s_b + SB_PLANE, rp, mp, PA);
+          QX = hann_x_power<false, true>(s_b + 8 * SB_PLANE, s_b + 7 * SB_PLANE, s_b + 7 * SB_PLANE, rp, mp, P8);
+        } else {
+          const lds_v2* c = s_b + pA * SB_PLANE;
+          QA = hann_x_power<false, false>(c, c - SB_PLANE, c + SB_PLANE, rp, mp, PA);
+        }
+        const lds_v2* c = s_b + pB * SB_PLANE;
+        QB = hann_x_power<false, false>(c, c - SB_PLANE, c + SB_PLANE, rp, mp, PB);
       } else {
-        QA = hann_x_power<0, false>(s_b, ky, pA, HA, PA);
+        const lds_v2* c = s_b + (pA + 1) * SB_PLANE;
+        QA = hann_x_power<false, false>(c, c - SB_PLANE, c + SB_PLANE, rp, mp, PA);
+        pass_done(QA);                     // one pass's LDS reads in flight at a time
+        QB = hann_x_power<false, false>(c + 4 * SB_PLANE, c + 3 * SB_PLANE, c + 5 * SB_PLANE, rp, mp, PB);
+        pass_done(QB);
+        const float4 u = ld4(s_b + oj), v = ld4(s_b + SB_PLANE + oj);
+        const float2 l0 = ld2(s_b + SB_PLANE + m0), l1 = ld2(s_b + SB_PLANE + m1);
+        const float q0 = hann_pow(f2(u.x, u.y), f2(l0.x, -l0.y), f2(v.x, v.y));
+        const float q1 = hann_pow(f2(u.z, u.w), f2(l1.x, -l1.y), f2(v.z, v.w));
+        wave_lds_sync();                   // the staged planes are read (s_p, s_q and s_t alias them)
+        st2(s_p + ky * 4 + r, f2(q0, q1));
+        wave_lds_sync();
+        if (r == 0) {
+          const float4 a0 = ld4(s_p + ky * 4), a1 = ld4(s_p + ky * 4 + 2);
+          const float P0[MZ] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+          QX = stageA(P0);
+        }
       }
-      QB = hann_x_power<0, false>(s_b, ky, pB, HB, PB);
       if (MODE == 1 || MODE == 2) {
         // learned-model input: x = ln(P + eps) - mean over all Mx*My*Mz bins,
         // eps = 1e-6 max P; stored for kx = 0..8 ([kx][ky][kz], BF16); bins
@@ -624,8 +708,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       // even/odd split in ky for stage B: slot 0 = Q(0), slots 1..7 = Q(k)+Q(-k),
       // slot 8 = Q(8), slots 9..15 = Q(16-j) - Q(j-16)... stored by the lane of
       // ky = j as Q(-ky') - Q(ky') with ky' = 16 - j
-      const float2 mA = row_neg(QA), mB = row_neg(QB), m8 = row_neg(Q8);
-      wave_lds_sync();                     // Hann-x reads of s_b are done (s_q aliases it)
+      const float2 mA = row_neg(QA), mB = row_neg(QB), mX = row_neg(QX);
+      if (FEAT) wave_lds_sync();           // Hann-x reads of s_b are done (s_q aliases it)
       {
         auto put = [&](int kx, float2 q, float2 m) {
           float2 v;
@@ -634,33 +718,42 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
           else v = f2(m.x - q.x, m.y - q.y);
           st2(&s_q[kx * MY + ky], v);
         };
-        put(pA, QA, mA);
-        put(pB, QB, mB);
-        if (r == 0) put(8, Q8, m8);
+        put(pA + KA, QA, mA);
+        put(pB + KA, QB, mB);
+        if (r == 0) put(FEAT ? 8 : 0, QX, mX);
       }
       wave_lds_sync();
 
       // ---- stage B: T(kx, l_y) = Q0 + Q8 cos(pi l) + sum_k A_k cos + j B_k sin
-      if (actB) {
-        float cB[7], sB[7], c8B;
-        {
-          const lds_float* tb = (const lds_float*)(s_tab) + iyB * 16;
+      // (the lane's Q row is read once for its up to three l_y)
+      if (kxB < NXH) {
+        float2 q[MY];
 #pragma unroll
-          for (int k = 0; k < 7; ++k) { cB[k] = tb[k]; sB[k] = tb[7 + k]; }
-          c8B = tb[14];
+        for (int k = 0; k < MY; k += 2) {
+          const float4 v = ld4(s_q + kxB * MY + k);
+          q[k] = f2(v.x, v.y);
+          q[k + 1] = f2(v.z, v.w);
         }
+        const lds_float* tb = s_tabB + gB * TABW;
+        lds_v2* pt = s_t + gB * TROW + kxB;
 #pragma unroll 1
-        for (int j = 0; j < 3; ++j) {
-          const int kx = 3 * gB + j;
-          const lds_v2* q = s_q + kx * MY;
-          float tx = q[0].x + c8B * q[8].x, ty = q[0].y + c8B * q[8].y;
+        for (int iy = gB; iy < nvy; iy += LB, tb += LB * TABW, pt += LB * TROW) {
+          float w[16];
+#pragma unroll
+          for (int k = 0; k < 16; k += 4) {
+            const v4f v = *reinterpret_cast<const lds_v4*>(tb + k);
+            w[k] = v.x;
+            w[k + 1] = v.y;
+            w[k + 2] = v.z;
+            w[k + 3] = v.w;
+          }
+          float tx = q[0].x + w[14] * q[8].x, ty = q[0].y + w[14] * q[8].y;
 #pragma unroll
           for (int k = 1; k < 8; ++k) {
-            const v2f A = q[k], Bv = q[16 - k];
-            tx += cB[k - 1] * A.x - sB[k - 1] * Bv.y;
-            ty += cB[k - 1] * A.y + sB[k - 1] * Bv.x;
+            tx += w[k - 1] * q[k].x - w[6 + k] * q[16 - k].y;
+            ty += w[k - 1] * q[k].y + w[6 + k] * q[16 - k].x;
           }
-          st2(&s_t[kx * NV1_MAX + iyB], f2(tx, ty));
+          st2(pt, f2(tx, ty));
         }
       }
       wave_lds_sync();
@@ -672,49 +765,70 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       float smv[MODE == 3 ? NC_IT : 1];    // mode 3: this lane's smoothed R, for the peak's neighbours
 #pragma unroll
       for (int j = 0; j < (MODE == 3 ? NC_IT : 1); ++j) smv[j] = 0.f;
-      if (actC) {
-        float cC[7], sC[7], c8C;
-        {
-          const lds_float* tc = (const lds_float*)(s_tab) + (4 * NV1_MAX + 4 * ixC) * 4;
+      auto stage_c = [&](auto kc) {
+        constexpr int KX = decltype(kc)::value;
+        constexpr int NR = (KX == 2) ? (NC_IT - 1) / 2 : NC_IT;
+        float w[KX][16];
 #pragma unroll
-          for (int k = 0; k < 7; ++k) { cC[k] = tc[k]; sC[k] = tc[7 + k]; }
-          c8C = tc[14];
-        }
+        for (int u = 0; u < KX; ++u) {
+          const lds_float* tc = s_tabC + min(ixC + u * LC, nvx - 1) * TABW;
 #pragma unroll
-        for (int j = 0; j < NC_IT; ++j) {
-          const int iy = hC + 3 * j;
-          if (iy < nvy) {
-            float rv = s_t[0 * NV1_MAX + iy].x + c8C * s_t[8 * NV1_MAX + iy].x;
-#pragma unroll
-            for (int kx = 1; kx < 8; ++kx) {
-              const v2f t = s_t[kx * NV1_MAX + iy];
-              rv += cC[kx - 1] * t.x - sC[kx - 1] * t.y;
-            }
-            const int w = iy * nvx + ixC;
-            float sm = rv;                   // learned mode: instantaneous R (no smoother state)
-            if (MODE != 2) {
-              sm = (1.f - a.alpha) * rv + a.alpha * rprev[j];
-              if (LAST) a.rsm[pix * nv + w] = sm;
-              else rprev[j] = sm;          // the pair's next frame smooths on from here
-            }
-            if (MODE == 3) smv[j] = sm;
-            amax_merge(bv, bi, sm, w);
+          for (int k = 0; k < 16; k += 4) {
+            const v4f v = *reinterpret_cast<const lds_v4*>(tc + k);
+            w[u][k] = v.x;
+            w[u][k + 1] = v.y;
+            w[u][k + 2] = v.z;
+            w[u][k + 3] = v.w;
           }
-          __builtin_amdgcn_sched_barrier(0);   // keep one iteration's LDS reads in flight at a time
         }
-      }
+        const lds_v2* pt = s_t + hC * TROW;
+        int iy = hC, w0 = wC;
+#pragma unroll
+        for (int v = 0; v < NR; ++v, iy += GC, w0 += GC * nvx, pt += GC * TROW) {
+          if (onC && iy < nvy) {
+            float2 t[NXH];
+#pragma unroll
+            for (int k = 0; k + 1 < NXH; k += 2) {
+              const float4 x4 = ld4(pt + k);
+              t[k] = f2(x4.x, x4.y);
+              t[k + 1] = f2(x4.z, x4.w);
+            }
+            t[8] = ld2(pt + 8);
+#pragma unroll
+            for (int u = 0; u < KX; ++u) {
+              if (KX == 2 && u == 1 && !second) continue;
+              float rv = t[0].x + w[u][14] * t[8].x;
+#pragma unroll
+              for (int kx = 1; kx < 8; ++kx) rv += w[u][kx - 1] * t[kx].x - w[u][6 + kx] * t[kx].y;
+              const int wi = w0 + u * LC;
+              float sm = rv;               // learned mode: instantaneous R (no smoother state)
+              if (MODE != 2) {
+                sm = (1.f - a.alpha) * rv + a.alpha * rprev[KX * v + u];
+                if (LAST) at(rq, 4u * (unsigned)wi) = sm;
+                else rprev[KX * v + u] = sm;   // the pair's next frame smooths on from here
+              }
+              if (MODE == 3) smv[KX * v + u] = sm;
+              amax_merge(bv, bi, sm, wi);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);   // one iteration's LDS reads in flight at a time
+        }
+      };
+      if (two) stage_c(std::integral_constant<int, 2>{});
+      else stage_c(std::integral_constant<int, 1>{});
       group_amax<64>(bv, bi);
       const int istar = (bi < nv) ? bi : 0;
       if (MODE == 2 && lane == 0) a.fidx[pix] = istar;
 
       // ---- mode 3: the peak refined between grid points; R at (ix, iy) is held
-      // by lane (iy mod 3) nvx + ix in its slot iy / 3
+      // by the lane and slot of its place in stage C
       float2 vref = f2(0.f, 0.f);
       if (MODE == 3) {
         const int best = __builtin_amdgcn_readfirstlane(istar);
         auto rv = [&](int w) -> float {
           const int iyn = w / nvx, ixn = w - iyn * nvx;
-          const int jn = iyn / 3, src = (iyn - 3 * jn) * nvx + ixn;
+          const int u = (two && ixn >= LC) ? 1 : 0, vn = iyn / GC;
+          const int jn = two ? 2 * vn + u : vn, src = (iyn - GC * vn) * LC + ixn - u * LC;
           float v = 0.f;
 #pragma unroll
           for (int j = 0; j < (MODE == 3 ? NC_IT : 1); ++j)
@@ -739,17 +853,21 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
         const int nq = a.latq[hsel];
         const int nxv = nq >> 16, nyv = (int)(short)(nq & 0xffff);
         const int qm = a.lat_q - 1;
-        const lds_v2* gA = s_g + ((nxv * pA + nyv * kyc) & qm) * MZ;
-        const lds_v2* gB = s_g + ((nxv * pB + nyv * kyc) & qm) * MZ;
-        const lds_v2* e = s_g + LATQ_MAX * MZ + pA * 17 + kyc + 8;   // plane pB = pA + 4
+        const lds_v2* gA = s_g + ((nxv * pA + nyv * kyc) & qm) * GROW;
+        const lds_v2* gB = s_g + ((nxv * pB + nyv * kyc) & qm) * GROW;
+        const lds_v2* e = s_g + LATQ_MAX * GROW + pA * 17 + kyc + 8;   // plane pB = pA + 4
         float2 sA = f2(0.f, 0.f), sB = f2(0.f, 0.f);
 #pragma unroll
-        for (int k = 0; k < MZ; ++k) {
-          const v2f g = gA[k], h = gB[k];
+        for (int k = 0; k < MZ; k += 2) {
+          const float4 g = ld4(gA + k), h = ld4(gB + k);
           sA.x += g.x * XA[k].x - g.y * XA[k].y;
           sA.y += g.x * XA[k].y + g.y * XA[k].x;
           sB.x += h.x * XB[k].x - h.y * XB[k].y;
           sB.y += h.x * XB[k].y + h.y * XB[k].x;
+          sA.x += g.z * XA[k + 1].x - g.w * XA[k + 1].y;
+          sA.y += g.z * XA[k + 1].y + g.w * XA[k + 1].x;
+          sB.x += h.z * XB[k + 1].x - h.w * XB[k + 1].y;
+          sB.y += h.z * XB[k + 1].y + h.w * XB[k + 1].x;
         }
         const float2 EA = ld2(e), EB = ld2(e + 4 * 17);
         acc = (EA.x * sA.x - EA.y * sA.y) + (EB.x * sB.x - EB.y * sB.y);
@@ -777,7 +895,8 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
           a.vxy[pix] = make_float2(a.fvx, a.fvy);
           a.vidx[pix] = -1;
         } else {
-          a.vxy[pix] = (MODE == 3) ? vref : make_float2(a.gx[istar % nvx], a.gy[istar / nvx]);
+          const int best = __builtin_amdgcn_readfirstlane(istar), iyb = (best * magic_nvx) >> 16;
+          a.vxy[pix] = (MODE == 3) ? vref : make_float2(s_gx[best - iyb * nvx], s_gx[nvx + iyb]);
           a.vidx[pix] = istar;
         }
       }

@@ -7,11 +7,11 @@
 namespace rmdf {
 namespace p16 {
 
-// Two workgroups (8 wavefronts) per CU: measured as fast as three, and the
-// 256-register budget keeps each wavefront's whole row (state, next row's
-// prefetched state) in registers.
+// Wavefronts per SIMD: two with the next row's state prefetched (256 registers)
+// for the modes bound by the state stream, three without (see rmdf_pixel16.h);
+// the direct form's LDS leaves room for two.
 template <int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_pixel16(PixArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE >= 3 && MODE != 5 ? 3 : 2))) k_pixel16(PixArgs a) {
   __shared__ __align__(16) char smem[smem16_bytes<MODE>()];
   const int xblocks = (a.W + WAVES - 1) / WAVES;
   pixel16_tile<MODE>(a, a.ring_delayed, blockIdx.x % xblocks, blockIdx.x / xblocks, smem);

@@ -28,6 +28,17 @@ __device__ __forceinline__ void st4(lds_v2* p, float a, float b, float c, float 
   *reinterpret_cast<lds_v4*>(p) = v4f{a, b, c, d};
 }
 
+// Element at a byte offset from a base that is the same in all lanes: a 32-bit
+// offset per lane instead of a 64-bit address.
+template <class T>
+static __device__ __forceinline__ const T& at(const T* base, unsigned bytes) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+template <class T>
+static __device__ __forceinline__ T& at(T* base, unsigned bytes) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
+}
+
 // Orders this wavefront's LDS accesses (lanes of one wavefront exchange
 // through LDS without a workgroup barrier).
 static __device__ __forceinline__ void wave_lds_sync() {
@@ -36,13 +47,15 @@ static __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// (bound_ctrl: every lane has a source in the patterns below, so no lane needs
+// its old value, and the move folds into the instruction that uses it)
 template <int CTRL>
 static __device__ __forceinline__ float dppf(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 static __device__ __forceinline__ int dppi(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
 }
 // row_ror:n -> dst[i] = src[(i - n) mod 16] within each row of 16 lanes;
 // row_mirror -> dst[i] = src[15 - i]; quad_perm [1,0,3,2] and [2,3,0,1] ->
@@ -93,26 +106,44 @@ static __device__ __forceinline__ float group_max(float v) {
   return (threadIdx.x & 32) ? fmaxf(r2, r3) : fmaxf(r0, r1);
 }
 
+// group minimum or maximum of an int (the comparison folds the DPP move)
+template <int G, bool MAX>
+static __device__ __forceinline__ int group_ext(int v) {
+  static_assert(G == 32 || G == 64, "groups of 32 or 64 lanes");
+  auto ext = [](int a, int b) { return MAX ? max(a, b) : min(a, b); };
+  v = ext(v, dppi<QXOR1>(v));
+  v = ext(v, dppi<QXOR2>(v));
+  v = ext(v, dppi<ROR4>(v));
+  v = ext(v, dppi<ROR8>(v));
+  const int r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
+  const int r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
+  if (G == 64) return ext(ext(r0, r1), ext(r2, r3));
+  return (threadIdx.x & 32) ? ext(r2, r3) : ext(r0, r1);
+}
+// an order-preserving map of float bits to int and back (its own inverse)
+static __device__ __forceinline__ int order_key(int b) { return b ^ ((b >> 31) & 0x7fffffff); }
+
+// The group's maximum v (never NaN: running maxima that began at -infinity)
+// and the lowest i that holds it: the maximum first, as an integer key (one DPP
+// instruction per level; a float maximum would quiet its operands first), then the index from the one lane that equals it, or from the lowest
+// where several do.
 template <int G>
 static __device__ __forceinline__ void group_amax(float& v, int& i) {
-  static_assert(G == 32 || G == 64, "groups of 32 or 64 lanes");
-  amax_merge(v, i, dppf<QXOR1>(v), dppi<QXOR1>(i));
-  amax_merge(v, i, dppf<QXOR2>(v), dppi<QXOR2>(i));
-  amax_merge(v, i, dppf<ROR4>(v), dppi<ROR4>(i));
-  amax_merge(v, i, dppf<ROR8>(v), dppi<ROR8>(i));
-  float va = lane_read(v, 0), vb = lane_read(v, 32);
-  int ia = __builtin_amdgcn_readlane(i, 0), ib = __builtin_amdgcn_readlane(i, 32);
-  amax_merge(va, ia, lane_read(v, 16), __builtin_amdgcn_readlane(i, 16));
-  amax_merge(vb, ib, lane_read(v, 48), __builtin_amdgcn_readlane(i, 48));
+  const float m = __int_as_float(order_key(group_ext<G, true>(order_key(__float_as_int(v)))));
+  const unsigned long long hold = __ballot(v == m);
+  const unsigned lo = (unsigned)hold, hi = (unsigned)(hold >> 32);
   if (G == 64) {
-    amax_merge(va, ia, vb, ib);
-    v = va;
-    i = ia;
+    if ((hold & (hold - 1)) == 0) i = __builtin_amdgcn_readlane(i, __builtin_ctzll(hold));
+    else i = group_ext<G, false>(v == m ? i : 0x7fffffff);
   } else {
-    const bool hi = (threadIdx.x & 32) != 0;
-    v = hi ? vb : va;
-    i = hi ? ib : ia;
+    if ((lo & (lo - 1)) == 0 && (hi & (hi - 1)) == 0) {
+      const int a = __builtin_amdgcn_readlane(i, __builtin_ctz(lo)), b = __builtin_amdgcn_readlane(i, 32 + __builtin_ctz(hi));
+      i = (threadIdx.x & 32) ? b : a;
+    } else {
+      i = group_ext<G, false>(v == m ? i : 0x7fffffff);
+    }
   }
+  v = m;
 }
 
 }  // namespace rmdf
