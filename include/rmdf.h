@@ -286,6 +286,21 @@ rmdf_status rmdf_mlp_infer_head(const void *h2, const float *W3, const float *b3
 rmdf_status rmdf_mlp_adam(float *p, const float *g, float *m, float *v, void *p_bf16, int n, float lr, float b1,
                           float b2, float eps, int step, void *stream);
 rmdf_status rmdf_mlp_to_bf16(const float *in, void *out_bf16, long long n, void *stream);
+/* Loss and every gradient of one batch of n samples (n a positive multiple of
+ * 8) in three launches: X[n][1152] BF16, labels[n][2], W1[128][1152] and
+ * W2[64][128] BF16, biases and W3[3][64] FP32, all device pointers (X, W1, W2
+ * 16-byte aligned).  Writes dW1, db1, dW2, db2, dW3, db3 (FP32, the shapes of
+ * the weights) and *loss (rmdf_mlp_head's loss).  The same rounding points and,
+ * within a sample, the same operation order as rmdf_mlp_gemm_nt, rmdf_mlp_head
+ * and their layer-by-layer backward pass; sums over samples run in a fixed
+ * order.  work: device scratch of rmdf_mlp_grads_work(n) bytes, 256-byte
+ * aligned, used until the stream has executed the call.
+ * Errors: RMDF_E_INVAL, RMDF_E_DEVICE. */
+rmdf_status rmdf_mlp_grads_work(int n, size_t *bytes);
+rmdf_status rmdf_mlp_grads(const void *X, const float *labels, int n, const void *W1, const float *b1, const void *W2,
+                           const float *b2, const float *W3, const float *b3, float wv, float half_step, float *dW1,
+                           float *db1, float *dW2, float *db2, float *dW3, float *db3, float *loss, void *work,
+                           size_t work_bytes, void *stream);
 
 /* Per-pixel kernel variant the context launches (1 generic, 2 one wavefront
  * per anchor), after resolving kernel_variant = 0. */

@@ -84,6 +84,8 @@ _SIGS = {
     "rmdf_mlp_adam": (_I, [_VP, _VP, _VP, _VP, _VP, _I, ctypes.c_float, ctypes.c_float, ctypes.c_float,
                            ctypes.c_float, _I, _VP]),
     "rmdf_mlp_to_bf16": (_I, [_VP, _VP, ctypes.c_longlong, _VP]),
+    "rmdf_mlp_grads_work": (_I, [_I, ctypes.POINTER(_SZ)]),
+    "rmdf_mlp_grads": (_I, [_VP, _VP, _I] + [_VP] * 6 + [ctypes.c_float] * 2 + [_VP] * 7 + [_VP, _SZ, _VP]),
     "rmdf_batch_create": (_I, [_I, _VP, ctypes.POINTER(rmdf_params), _VP, ctypes.POINTER(_VP)]),
     "rmdf_batch_input": (_I, [_VP, _I, ctypes.POINTER(_VP)]),
     "rmdf_batch_launch": (_I, [_VP]),
@@ -591,6 +593,23 @@ def mlp_adam(p, g, m, v, p_bf16, lr, step, b1=0.9, b2=0.999, eps=1e-8):
 
 def mlp_to_bf16(inp, out):
     _check(lib().rmdf_mlp_to_bf16(inp.data_ptr(), out.data_ptr(), inp.numel(), ctypes.c_void_p(_stream_handle())))
+
+
+def mlp_grads_work(n: int) -> int:
+    """Bytes of device scratch mlp_grads needs for n samples."""
+    b = ctypes.c_size_t()
+    _check(lib().rmdf_mlp_grads_work(int(n), ctypes.byref(b)))
+    return b.value
+
+
+def mlp_grads(X, labels, W1, b1, W2, b2, W3, b3, wv, half_step, grads, loss, work):
+    """rmdf_mlp_grads: loss and gradients of one batch; grads: dict of FP32
+    tensors W1, b1, W2, b2, W3, b3; work: uint8 scratch."""
+    g = [grads[k].data_ptr() for k in ("W1", "b1", "W2", "b2", "W3", "b3")]
+    _check(lib().rmdf_mlp_grads(X.data_ptr(), labels.data_ptr(), X.shape[0], W1.data_ptr(), b1.data_ptr(),
+                                W2.data_ptr(), b2.data_ptr(), W3.data_ptr(), b3.data_ptr(), float(wv),
+                                float(half_step), *g, loss.data_ptr(), work.data_ptr(), work.numel(),
+                                ctypes.c_void_p(_stream_handle())))
 
 
 def cfar(x, guard: int, train: int, k: float, want_level: bool = False):

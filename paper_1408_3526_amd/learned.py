@@ -130,13 +130,8 @@ class Trainer:
         b.mlp_to_bf16(self.p["W2"], self.bf["W2"])
         self.lr, self.wv, self.half_step, self.batch = lr, wv, half_step, batch
         self.step_n = 0
-        B = batch
-        bf16 = torch.bfloat16
-        self.buf = {"H1": torch.empty(B, N_H1, dtype=bf16, device=dev), "H2": torch.empty(B, N_H2, dtype=bf16, device=dev),
-                    "dH2": torch.empty(B, N_H2, dtype=bf16, device=dev), "dH1": torch.empty(B, N_H1, dtype=bf16, device=dev),
-                    "dH2t": torch.empty(N_H2, B, dtype=bf16, device=dev), "H1t": torch.empty(N_H1, B, dtype=bf16, device=dev),
-                    "dH1t": torch.empty(N_H1, B, dtype=bf16, device=dev), "Xt": torch.empty(N_IN, B, dtype=bf16, device=dev),
-                    "W2t": torch.empty(N_H1, N_H2, dtype=bf16, device=dev),
+        # scratch of a batch's forward and backward pass, and its loss
+        self.buf = {"work": torch.empty(b.mlp_grads_work(-(-batch // 8) * 8), dtype=torch.uint8, device=dev),
                     "loss": torch.zeros(1, device=dev)}
 
     def forward(self, X, H1, H2):
@@ -146,29 +141,12 @@ class Trainer:
 
     def grads(self, X, lab):
         """Loss and gradients of one batch (into self.g); returns the loss tensor."""
-        b, u = self.b, self.buf
-        n = X.shape[0]
-        H1, H2, dH2, dH1 = u["H1"][:n], u["H2"][:n], u["dH2"][:n], u["dH1"][:n]
-        self.forward(X, H1, H2)
-        for k in ("W3", "b3"):
-            self.g[k].zero_()
-        u["loss"].zero_()
-        b.mlp_head(H2, self.p["W3"], self.p["b3"], lab, self.wv, self.half_step, dH2, self.g["W3"], self.g["b3"],
-                   u["loss"])
-        dH2t, H1t, dH1t, Xt = u["dH2t"][:, :n], u["H1t"][:, :n], u["dH1t"][:, :n], u["Xt"][:, :n]
-        if n != self.batch:
-            dH2t, H1t, dH1t, Xt = (self.torch.empty(t.shape[0], n, dtype=self.torch.bfloat16, device="cuda")
-                                   for t in (dH2t, H1t, dH1t, Xt))
-        b.mlp_transpose(dH2, dH2t)
-        b.mlp_transpose(H1, H1t)
-        b.mlp_gemm_nt(dH2t, H1t, out_f32=self.g["W2"])                         # dW2 = dH2^T H1
-        b.mlp_colsum(dH2, self.g["b2"])
-        b.mlp_transpose(self.bf["W2"], u["W2t"])
-        b.mlp_gemm_nt(dH2, u["W2t"], epi=2, aux=H1, out_bf16=dH1)              # dH1 = dH2 W2 * (H1 > 0)
-        b.mlp_transpose(dH1, dH1t)
-        b.mlp_transpose(X, Xt)
-        b.mlp_gemm_nt(dH1t, Xt, out_f32=self.g["W1"])                          # dW1 = dH1^T X
-        b.mlp_colsum(dH1, self.g["b1"])
+        b, u, p = self.b, self.buf, self.p
+        work = u["work"]
+        if X.shape[0] != self.batch:
+            work = self.torch.empty(b.mlp_grads_work(X.shape[0]), dtype=self.torch.uint8, device="cuda")
+        b.mlp_grads(X, lab, self.bf["W1"], p["b1"], self.bf["W2"], p["b2"], p["W3"], p["b3"], self.wv, self.half_step,
+                    self.g, u["loss"], work)
         return u["loss"]
 
     def step(self, X, lab):
