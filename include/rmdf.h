@@ -218,7 +218,8 @@ rmdf_status rmdf_smoothed_r(rmdf_ctx *ctx, float *rs_dev);
 
 /* Per-kernel timing with HIP events on the context stream (off by default).
  * which: 0 = pixel kernel, 1 = row sliding-DFT kernel (which also copies the
- * frame into the delay ring), 2 = unused (no separate ingest kernel),
+ * frame into the delay ring; none where the generic kernel's tiles do both
+ * themselves), 2 = unused (no separate ingest kernel),
  * 3 = learned-model network (the confident-anchor count reset and the
  * network kernel), 4 = learned-mode finish kernel.
  * rmdf_set_timing: mask bit w times kernel w; 0 = off, -1 = all (each timed

@@ -168,10 +168,11 @@ static __device__ void row_chunk(const float* __restrict__ f, float2* __restrict
 // instead of one per 64 candidates), and the planes beyond the half spectrum
 // are stored as mirrors so that the Hann pass along kx reads fixed offsets.
 // Against the form with workgroup barriers and loads in the candidate loop
-// (us per frame, output and velocity read): 9x9x5 640x512 941 -> 527 (VALU 69%
+// (us per frame, output and velocity read): 9x9x5 640x512 941 -> 505 (VALU 69%
 // busy, 659 instructions an anchor; the state and R traffic alone would take
-// 370), 8x8x4 640x512 397 -> 241, 16x16x8 319x241 with 33x33 candidates
-// 1243 -> 714, the paper's 64x64 frames 24.4 -> 21.4.
+// 370), 8x8x4 640x512 397 -> 240, 16x16x8 319x241 with 33x33 candidates
+// 1243 -> 630, the paper's 64x64 frames 24.4 -> 19.4 (the row spectra computed in
+// the tiles are 16, 0, 10 and 1.8 of these).
 template <int MX, int MY, int MZ>
 struct Shape {
   static constexpr bool EVEN = (MX % 2 == 0);
@@ -192,8 +193,17 @@ struct Shape {
   static constexpr int S_ELEMS = (NXH + 2) * MY * MZP;      // staged planes kx = -1 .. Mx/2 + 1 (float2)
   static constexpr int QT_ELEMS = NXH * MYQ + NVY_MAX * NXT;
   static constexpr int W_ELEMS = PPW * (S_ELEMS > QT_ELEMS ? S_ELEMS : QT_ELEMS);   // per wavefront
-  static constexpr int TAB_ELEMS = NVY_MAX * MYT + NVX_MAX * NXT + MYQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;
+  static constexpr int MXQ = (MX + 1) / 2 * 2;
+  static constexpr int TAB_ELEMS = NVY_MAX * MYT + NVX_MAX * NXT + MYQ + MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;
+  // row spectra of SR rows and the My above them for the workgroup's anchors;
+  // the samples they come from (one resonator segment and the Mx before it)
+  // lie in the wavefronts' staging area while it is idle
+  static constexpr int SR = 32;
+  static constexpr int RS_ELEMS = ((SR + MY) * PPB * NP + 1) / 2 * 2;
+  static constexpr int SW = MX + RSEG + (MX % 2 ? 3 : 4);   // floats per sample row: 16-byte aligned, spread over banks
+  static_assert((SR + MY) * SW <= 2 * WAVES * W_ELEMS, "samples fit the staging area");
   static constexpr size_t SMEM = sizeof(float2) * (TAB_ELEMS + WAVES * W_ELEMS);
+  static constexpr size_t SMEM_ROWS = SMEM + sizeof(float2) * RS_ELEMS;   // tiles that compute their row spectra
 };
 
 
@@ -218,10 +228,109 @@ static __device__ __forceinline__ float2 coeff_at(int kx, int ky, int kz, float 
   return make_float2(g * cs, g * sn);
 }
 
+// Row spectra of rows [ya, ya + rows) for the PPB columns from x0 (all in one
+// resonator segment: PPB divides RSEG) into s_rs[row][column][plane]: the
+// values of row_chunk, bit for bit (the segment's direct-DFT seed, then the
+// comb and resonator up to each column).  Non-finite samples read as 0; those
+// of rows from yc on are counted, and the columns of those rows are stored in
+// the frame's delay-ring slot.  All threads of the workgroup call it; the caller
+// has a barrier before (s_in idle) and gets one after.
+template <int MX, int MY, int MZ>
+static __device__ __forceinline__ void tile_rows(const PixArgs& a, int x0, int ya, int yc, int rows, lds_float* s_in,
+                                                 const lds_v2* s_twx, lds_v2* s_rs) {
+  const float* __restrict__ f = a.frame;
+  float* __restrict__ slot = a.slot;
+  using SH = Shape<MX, MY, MZ>;
+  constexpr int NP = SH::NP, SW = SH::SW, PPB = SH::PPB;
+  const int xs = x0 / RSEG * RSEG, o0 = x0 - xs;            // segment start; first own column in it
+  int bad = 0;
+  for (int i = threadIdx.x; i < rows * (MX + RSEG); i += 256) {
+    const int row = i / (MX + RSEG), c = i - row * (MX + RSEG);
+    const int yy = ya + row, xx = xs - MX + c;
+    float v = (yy >= 0 && xx >= 0 && xx < a.W) ? f[(size_t)yy * a.W + xx] : 0.0f;
+    const bool own = yy >= yc && c >= MX + o0 && c < MX + o0 + PPB && xx < a.W;
+    if (!isfinite(v)) {
+      v = 0.0f;
+      bad += own ? 1 : 0;
+    }
+    s_in[row * SW + c] = v;
+    if (own) slot[(size_t)yy * a.W + xx] = v;
+  }
+  // the wavefront's count, reduced only where it has non-finite samples
+  if (__ballot(bad != 0)) {
+    int tot = bad;
+    for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(a.nonfinite, (unsigned long long)tot);
+  }
+  __syncthreads();
+  const float inv = rsqrtf((float)MX);
+  // one (plane, row) per thread, plane by plane; its samples and twiddles are
+  // all read before the recursion, whose steps then wait for nothing
+  for (int t = threadIdx.x; t < rows * NP; t += 256) {
+    const int p = t / rows, row = t - p * rows;
+    float in[MX + RSEG + 3];
+#pragma unroll
+    for (int c = 0; c < MX + RSEG; c += 4) {
+      const v4f q = *reinterpret_cast<const lds_v4*>(s_in + row * SW + c);
+      in[c] = q.x;
+      in[c + 1] = q.y;
+      in[c + 2] = q.z;
+      if (c + 3 < MX + RSEG + 3) in[c + 3] = q.w;
+    }
+    lds_v2* out = s_rs + row * (PPB * NP) + p;
+    if (p == 0) {
+      float a0 = 0.f, ah = 0.f;
+#pragma unroll
+      for (int m = 0; m < MX; ++m) {
+        const float v = in[MX - 1 - m];
+        a0 += v;
+        ah += (m & 1) ? -v : v;
+      }
+#pragma unroll
+      for (int i = 0; i < RSEG; ++i) {
+        if (i < o0 + PPB) {                                // uniform
+          const float comb = in[MX + i] - in[i];
+          a0 = a0 + comb;
+          ah = -ah + comb;
+          if (i >= o0) st2(out + (i - o0) * NP, SH::EVEN ? make_float2(a0 * inv, ah * inv) : make_float2(a0 * inv, 0.f));
+        }
+      }
+    } else {
+      float2 w[MX];
+      int e = 0;                                           // (p m) mod Mx
+#pragma unroll
+      for (int m = 0; m < MX; ++m) {
+        w[m] = ld2(s_twx + e);
+        e += p;
+        e = (e >= MX) ? e - MX : e;
+      }
+      float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+      for (int m = 0; m < MX; ++m) {
+        const float v = in[MX - 1 - m];
+        acc.x += w[m].x * v;
+        acc.y += w[m].y * v;
+      }
+#pragma unroll
+      for (int i = 0; i < RSEG; ++i) {
+        if (i < o0 + PPB) {                                // uniform
+          const float comb = in[MX + i] - in[i];
+          acc = cmul(w[1], acc);
+          acc.x += comb;
+          if (i >= o0) st2(out + (i - o0) * NP, cscale(acc, inv));
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
 // One work tile: PPB adjacent anchor columns starting at xb*PPB, rows
 // [yb*TY, yb*TY + TY).  All 256 threads of the block must call it.
-// REFINED: velocity mode 3 (its eq. 8 per bin needs many registers).
-template <int MX, int MY, int MZ, bool REFINED = false>
+// REFINED: velocity mode 3 (its eq. 8 per bin needs many registers).  OWN_ROWS:
+// the tile computes its row spectra from a.frame, and stores its part of the
+// frame into the delay ring; otherwise they come from the row kernel (a.rs).
+template <int MX, int MY, int MZ, bool REFINED = false, bool OWN_ROWS = false>
 static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float* ring_delayed, int xb, int yb, char* smem) {
   using SH = Shape<MX, MY, MZ>;
   constexpr int NP = SH::NP, NXH = SH::NXH, NCOL = SH::NCOL, LPP = SH::LPP, CPL = SH::CPL, PPW = SH::PPW;
@@ -235,23 +344,30 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ps = (PPW == 1) ? 0 : lane / LPP;
   const int cl = (PPW == 1) ? lane : lane % LPP;           // lane within the anchor
-  lds_float* s_gx = (lds_float*)(s_twy + MYQ);   // [nvx], then gy [nvy]
-  lds_v2* s_w = s_twy + MYQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2 + wv * SH::W_ELEMS + ps * (SH::W_ELEMS / PPW);
+  lds_v2* s_twx = s_twy + MYQ;                   // [MX]
+  lds_float* s_gx = (lds_float*)(s_twx + SH::MXQ);   // [nvx], then gy [nvy]
+  lds_v2* s_rs = s_twx + SH::MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;   // [SR + MY][PPB][NP]
+  lds_v2* s_w0 = s_rs + (OWN_ROWS ? SH::RS_ELEMS : 0);
+  lds_v2* s_w = s_w0 + wv * SH::W_ELEMS + ps * (SH::W_ELEMS / PPW);
   const int nvx = a.nvx, nvy = a.nvy, nv = a.nv;
   for (int i = tid; i < MY; i += 256) s_twy[i] = v2f{a.twy[i].x, a.twy[i].y};
   for (int i = tid; i < nvy * MY; i += 256) s_tauy[i / MY * MYT + i % MY] = v2f{a.tauy[i].x, a.tauy[i].y};
   for (int i = tid; i < nvx * NXH; i += 256) s_taux[i / NXH * NXT + i % NXH] = v2f{a.taux[i].x, a.taux[i].y};
+  for (int i = tid; i < MX; i += 256) s_twx[i] = v2f{a.twx[i].x, a.twx[i].y};
   for (int i = tid; i < nvx + nvy; i += 256) s_gx[i] = (i < nvx) ? a.gx[i] : a.gy[i - nvx];
-  __syncthreads();                               // the only workgroup barrier
 
   const int y0 = yb * a.TY;
   const int y1 = min(a.H, y0 + a.TY);
   const int xw = xb * SH::PPB + wv * PPW;         // the wavefront's first anchor
-  if (xw >= a.W || y0 >= y1) return;             // whole wavefront leaves
+  const bool active = xw < a.W;
+  if (!OWN_ROWS) {
+    __syncthreads();                             // the only workgroup barrier
+    if (!active) return;                         // (OWN_ROWS: an idle wavefront still stages rows)
+  }
   // the second anchor of a pair past the frame's edge repeats the last column
   // without storing; lanes past the last column repeat it
   const bool px_ok = xw + ps < a.W;
-  const int dxw = px_ok ? ps : a.W - 1 - xw;
+  const int dxw = px_ok ? ps : max(a.W - 1 - xw, 0);
   const int x = xw + dxw;
   int p[CPL], ky[CPL], col[CPL];
 #pragma unroll
@@ -261,12 +377,16 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     ky[j] = col[j] % MY;
   }
   // addresses: a base per row (the same in all lanes) and a 32-bit offset per lane
-  unsigned so[CPL], ro[CPL];
+  unsigned so[CPL];
+  unsigned ro[CPL];
+  const lds_v2* rs_own[CPL];                     // this column's row spectrum, row 0 of s_rs
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
     so[j] = (unsigned)((dxw * NCOL + col[j]) * MZ) * 8u;
     ro[j] = (unsigned)(dxw * NP + p[j]) * 8u;
+    rs_own[j] = s_rs + (wv * PPW + dxw) * NP + p[j];
   }
+  constexpr int RSR = SH::PPB * NP;              // s_rs row
   const unsigned qo = (unsigned)(dxw * nv) * 4u;
   const bool st_ok = px_ok && cl < NCOL;         // (CPL > 1: every lane's columns exist)
 
@@ -276,17 +396,9 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   lds_v2* s_t = s_w + NXH * MYQ;                 // [nvy][NXT]
 
   // Column sliding DFT: seed with the direct DFT of the My rows above y0
-  // (rows above the frame count as zero).  All My loads are issued before the
-  // sum, so a tile start costs one memory latency, not My of them.
+  // (rows above the frame count as zero)
   float2 acol[CPL], wy[CPL];
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    float2 v[MY];
-#pragma unroll
-    for (int m = 0; m < MY; ++m) {
-      const int yy = y0 - 1 - m;
-      v[m] = (yy >= 0) ? at(a.rs + ((size_t)yy * a.W + xw) * NP, ro[j]) : make_float2(0.f, 0.f);
-    }
+  auto seed = [&](int j, const float2 (&v)[MY]) {
     acol[j] = make_float2(0.f, 0.f);
     int e = 0;                                   // (ky m) mod My
 #pragma unroll
@@ -296,6 +408,20 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
       e = (e >= MY) ? e - MY : e;
     }
     wy[j] = ld2(&s_twy[ky[j]]);
+  };
+  if (!OWN_ROWS) {
+    // all My loads are issued before the sum, so a tile start costs one memory
+    // latency, not My of them
+#pragma unroll
+    for (int j = 0; j < CPL; ++j) {
+      float2 v[MY];
+#pragma unroll
+      for (int m = 0; m < MY; ++m) {
+        const int yy = y0 - 1 - m;
+        v[m] = (yy >= 0) ? at(a.rs + ((size_t)yy * a.W + xw) * NP, ro[j]) : make_float2(0.f, 0.f);
+      }
+      seed(j, v);
+    }
   }
 
   // the same in every lane: held in scalar registers
@@ -310,8 +436,7 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     twA[k] = uni(a.twA[k]);
   }
 
-  // first row's state and row-spectrum samples; later rows' are loaded one
-  // row ahead
+  // first row's state (and row spectra); later rows' are loaded one row ahead
   float2 Xn[CPL][MZ], in_n[CPL], in_o[CPL];
   auto load_row = [&](int y) {
     const float2* src = a.st + ((size_t)y * a.W + xw) * (NCOL * MZ);
@@ -319,13 +444,16 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     const float2* rl = a.rs + ((size_t)max(y - MY, 0) * a.W + xw) * NP;
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
+      const float2* s = &at(src, so[j]);         // (one address: the loads merge to 16 bytes)
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) Xn[j][k] = at(src, so[j] + 8u * k);
-      in_n[j] = at(rn, ro[j]);
-      in_o[j] = at(rl, ro[j]);
+      for (int k = 0; k < MZ; ++k) Xn[j][k] = s[k];
+      if (!OWN_ROWS) {
+        in_n[j] = at(rn, ro[j]);
+        in_o[j] = at(rl, ro[j]);
+      }
     }
   };
-  load_row(y0);
+  if (active) load_row(y0);
 
   // The lane's place in stages B (item kx * nvy + iy) and C (item iy * nvx + ix).
   // One column per lane: items cl, cl + LPP, ..., the pair of indices moving by
@@ -348,12 +476,31 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   constexpr int NB = 6;                          // candidates per lane whose smoothed R is loaded together
   const float inv_nvx = 1.0f / (float)nvx;
 
-  for (int y = y0; y < y1; ++y) {
+  for (int yc = y0; yc < y1; yc += SH::SR) {      // OWN_ROWS: SR rows of row spectra at a time
+   const int ye = OWN_ROWS ? min(y1, yc + SH::SR) : y1;
+   if (OWN_ROWS) {
+    if (yc > y0) __syncthreads();                // every wavefront is done with the previous rows
+    tile_rows<MX, MY, MZ>(a, xb * SH::PPB, yc - MY, yc, ye - yc + MY, (lds_float*)s_w0, s_twx, s_rs);
+    if (!active) continue;
+    if (yc == y0) {
+#pragma unroll
+     for (int j = 0; j < CPL; ++j) {
+      float2 v[MY];
+#pragma unroll
+      for (int m = 0; m < MY; ++m)
+        v[m] = (y0 - 1 - m >= 0) ? ld2(rs_own[j] + (MY - 1 - m) * RSR) : make_float2(0.f, 0.f);
+      seed(j, v);
+     }
+    }
+   }
+   for (int y = yc; y < ye; ++y) {
     const size_t pix0 = (size_t)y * a.W + xw;     // the same in all lanes
-    // opaque per row: what stage C derives from the lane's place is computed
-    // again each row instead of being held in registers across the loop
-    int iyC = iyC0, ixC = ixC0;
+    const int r0 = (y - yc) * RSR;
+    // opaque per row: what stage C derives from the lane's place is computed again each
+    // row instead of being held in registers (or spilled) across the loop
+    int iyC = iyC0, ixC = ixC0, wC = cl;
     if (ROWS) asm volatile("" : "+v"(iyC), "+v"(ixC));
+    else asm volatile("" : "+v"(wC));
     float2 X[CPL][MZ];
     float* rp = a.rsm + pix0 * nv;
     float rn[NB];
@@ -367,8 +514,8 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
       // ---- column sliding DFT: comb on the row spectra, resonator w_y^ky
-      float2 in = in_n[j];
-      if (y >= MY) in = csub(in, in_o[j]);
+      float2 in = OWN_ROWS ? ld2(rs_own[j] + r0 + MY * RSR) : in_n[j];
+      if (y >= MY) in = csub(in, OWN_ROWS ? ld2(rs_own[j] + r0) : in_o[j]);
       acol[j] = cadd(cmul(wy[j], acol[j]), in);
       const float2 s2 = cscale(acol[j], a.inv_sqrt_my);
       // ---- temporal deadbeat observer: prior = rotate(posterior), innovation
@@ -383,15 +530,15 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
 #pragma unroll
       for (int k = 0; k < MZ; ++k) X[j][k] = cadd(X[j][k], e);
       if (st_ok) {
-        float2* dst = a.st + pix0 * (NCOL * MZ);
+        float2* dst = &at(a.st + pix0 * (NCOL * MZ), so[j]);
 #pragma unroll
-        for (int k = 0; k < MZ; ++k) at(dst, so[j] + 8u * k) = X[j][k];
+        for (int k = 0; k < MZ; ++k) dst[k] = X[j][k];
       }
     }
     // this row's smoothed R (first rounds of stage C), the delayed sample and
     // the next row's state are in flight during the flow stages; stage C waits
     // for the first group only (vector memory completes in order)
-    load_r(ROWS ? iyC : cl);
+    load_r(ROWS ? iyC : wC);
     float idel = 0.f;
     {
       const int xs = x - a.dx, ys = y - a.dy;
@@ -503,7 +650,12 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     };
     float2 Q[CPL], Qh = make_float2(0.f, 0.f);
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) Q[j] = stage_a(p[j], ky[j]);
+    for (int j = 0; j < CPL; ++j) {
+      Q[j] = stage_a(p[j], ky[j]);
+      // one pass's LDS reads in flight at a time: with both in flight the 16x16x8
+      // tile spilled (33x33 candidates at 319x241: 631 against 676 us a frame)
+      if (CPL > 1) pass_done(Q[j]);
+    }
     if (EVEN) {
       if (cl < MY) Qh = stage_a(MX / 2, ky[0]);
     }
@@ -597,13 +749,13 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
         const lds_v2* p_x = s_taux + o_xC;
         for (int w0 = 0; w0 < nv; w0 += NB * LPP) {
           next();
-          if (w0 + NB * LPP < nv) load_r(w0 + NB * LPP + cl);
+          if (w0 + NB * LPP < nv) load_r(w0 + NB * LPP + wC);
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
             if (w0 + i * LPP < nv) {             // uniform: some lane has a candidate
               ld_col<NXH>(s_t + min(o_t, t_last), t);
               ld_col<NXH>(p_x, tx[0]);
-              const int w = w0 + i * LPP + cl;
+              const int w = w0 + i * LPP + wC;
               if (w < nv) item(tx[0], rc[i], w);
               ix += dxC;
               const int carry = (ix >= nvx) ? -1 : 0;
@@ -653,7 +805,7 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
           const unsigned h0 = __umul24(__umul24(hsel, a.bx + 1) + p[j], 2 * a.by + 1) * (8u * MZ) + (kyc + a.by) * (8u * MZ);
 #pragma unroll
           for (int kz = 0; kz < MZ; ++kz) {
-            const float2 h = at(a.htab, h0 + 8u * kz);
+            const float2 h = (&at(a.htab, h0))[kz];
             acc += h.x * X[j][kz].x - h.y * X[j][kz].y;
           }
         }
@@ -673,6 +825,8 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
         a.vidx[pix] = istar;
       }
     }
+   }
+   if (!OWN_ROWS) break;
   }
 }
 

@@ -289,6 +289,7 @@ rmdf::PixArgs rmdf_internal_pixargs(const rmdf_ctx* c) {
   a.alpha = c->alpha; a.inv_sqrt_my = (float)(1.0 / std::sqrt((double)c->MY));
   a.fvx = c->fvx; a.fvy = c->fvy;
   a.rs = c->rs; a.st = c->st; a.rsm = c->rsm;
+  a.nonfinite = c->nonfinite; a.twx = c->twx;
   a.ring_delayed = nullptr;
   a.out = c->out; a.vxy = c->vxy; a.vidx = c->vidx;
   a.twy = c->twy; a.twz = c->twz; a.twA = c->twA; a.tauy = c->tauy; a.taux = c->taux; a.htab = c->htab;
@@ -529,16 +530,24 @@ rmdf_status rmdf_push_frame(rmdf_ctx* c, const float* frame) {
   float* slot = c->ring + HW * (size_t)(c->t % c->nring);
   EventPair ev{};
   hipError_t e;
-  // row sliding DFT straight from the caller's frame; the same kernel stores
-  // the frame (non-finite samples zeroed and counted) into the delay ring
-  timed_begin(c, 1, &ev);
-  e = rmdf::launch_row(c->MX, frame, c->rs, c->twx, c->H, c->W, slot, c->nonfinite, c->stream,
-                       c->temporal == RMDF_TEMPORAL_DIRECT);
-  timed_end(c, &ev);
-  if (e != hipSuccess) return hip_fail(c, e, "row kernel launch");
-
   rmdf::PixArgs a = rmdf_internal_pixargs(c);
+  const bool rows_in_tiles = c->variant != 2 && rmdf::tiles_compute_rows(c->MX, c->H, c->W, c->TY, c->vmode == RMDF_VEL_REFINED);
+  if (!rows_in_tiles) {
+    // row sliding DFT straight from the caller's frame; the same kernel stores
+    // the frame (non-finite samples zeroed and counted) into the delay ring
+    timed_begin(c, 1, &ev);
+    e = rmdf::launch_row(c->MX, frame, c->rs, c->twx, c->H, c->W, slot, c->nonfinite, c->stream,
+                         c->temporal == RMDF_TEMPORAL_DIRECT);
+    timed_end(c, &ev);
+    if (e != hipSuccess) return hip_fail(c, e, "row kernel launch");
+  } else {
+    a.frame = frame;               // the tiles do both themselves
+    a.slot = slot;
+  }
   a.ring_delayed = (c->t >= c->dt) ? c->ring + HW * (size_t)((c->t - c->dt) % c->nring) : nullptr;
+  // no delay: the tiles are storing that slot in this launch (the kernels read a
+  // non-finite delayed sample as 0)
+  if (rows_in_tiles && c->dt == 0) a.ring_delayed = frame;
   const int mode = (c->temporal == RMDF_TEMPORAL_DIRECT) ? 5
                    : (c->temporal == RMDF_TEMPORAL_RING) ? 4
                    : (c->vmode == RMDF_VEL_LEARNED) ? 2

@@ -19,6 +19,10 @@ struct PixArgs {
   float alpha, inv_sqrt_my;
   float fvx, fvy;
   const float2* rs;            // row spectra [H][W][planes]
+  const float* frame;          // generic kernel: nullptr, or the frame, from which its tiles then
+  float* slot;                 // compute the row spectra themselves, store it into its delay-ring
+  unsigned long long* nonfinite;   // slot (non-finite samples zeroed and counted in *nonfinite);
+  const float2* twx;           // [Mx] w_x^k
   float2* st;                  // observer state [H][W][planes*My][Mz] (16x16x8 wave-per-anchor
                                // kernel: [H][W][Mz/2][planes*My][2])
   float* rsm;                  // smoothed autocorrelation [H][W][nv]
@@ -64,6 +68,19 @@ int pixel_block_columns(int mx, int my, int mz);
 // default rows per work tile for an H x W frame
 int auto_tile_rows(int H, int W, int block_columns);
 hipError_t launch_pixel(int mx, int my, int mz, const PixArgs& a, hipStream_t s);
+// Whether the generic kernel's tiles compute their row spectra themselves
+// (PixArgs::frame) instead of reading the row kernel's.  They save a launch and
+// its latency and the row spectra's way through memory, and wait longer at
+// their start for My + TY rows (us per frame, row kernel against own rows):
+//   9x9x5   64x64 TY 1 15.6 / 13.6, 128x128 TY 2 33.2 / 33.0, 320x256 TY 8
+//           145 / 140, 640x512 TY 32 516 / 496: always
+//   16x16x8 (25x25 candidates) 80x64 TY 1 49 / 68, 160x128 TY 4 170 / 178, 240x180
+//           TY 8 326 / 318, 320x256 TY 16 611 / 549: from TY = 8 on
+//   8x8x4   64x64 TY 1 12.0 / 10.5, 160x128 TY 1 25.5 / 30.7, 320x256 TY 4 70 / 76,
+//           640x512 TY 16 236 / 237, 960x720 TY 32 475 / 467: tall tiles, and one-row
+//           tiles that are all resident at once
+//   refined velocity (9x9x5 317x243): 212 / 217: never
+bool tiles_compute_rows(int mx, int H, int W, int TY, bool refined);
 // row sliding DFT of the frame f; also copies f into the delay-ring slot
 // (non-finite samples zeroed and counted in *nonfinite).  direct: each output
 // is the direct DFT sum of its window instead (Mx = 16 only)

@@ -41,12 +41,12 @@ __global__ void __launch_bounds__(256) k_row(const float* __restrict__ f, float2
   row_chunk<MX, DIRECT>(f, rs, twx, H, W, blockIdx.y, blockIdx.x * RCX, smem, nonfinite, slot);
 }
 
-template <int MX, int MY, int MZ, bool REFINED>
+template <int MX, int MY, int MZ, bool REFINED, bool OWN_ROWS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MZ == 8 ? 2 : 4))) k_pixel(PixArgs a) {
   using SH = Shape<MX, MY, MZ>;
-  __shared__ __align__(16) char smem[SH::SMEM];
+  __shared__ __align__(16) char smem[OWN_ROWS ? SH::SMEM_ROWS : SH::SMEM];
   const int xblocks = (a.W + SH::PPB - 1) / SH::PPB;
-  pixel_tile<MX, MY, MZ, REFINED>(a, a.ring_delayed, blockIdx.x % xblocks, blockIdx.x / xblocks, smem);
+  pixel_tile<MX, MY, MZ, REFINED, OWN_ROWS>(a, a.ring_delayed, blockIdx.x % xblocks, blockIdx.x / xblocks, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -105,8 +105,13 @@ static hipError_t launch_pixel_t(const PixArgs& a, hipStream_t s) {
   using SH = Shape<MX, MY, MZ>;
   const int xblocks = (a.W + SH::PPB - 1) / SH::PPB;
   const int yblocks = (a.H + a.TY - 1) / a.TY;
-  if (a.vmode == 3) hipLaunchKernelGGL((k_pixel<MX, MY, MZ, true>), dim3(xblocks * yblocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_pixel<MX, MY, MZ, false>), dim3(xblocks * yblocks), dim3(256), 0, s, a);
+  const dim3 grid(xblocks * yblocks), block(256);
+  if (a.vmode == 3) {
+    hipLaunchKernelGGL((k_pixel<MX, MY, MZ, true, false>), grid, block, 0, s, a);
+  } else {
+    if (a.frame) hipLaunchKernelGGL((k_pixel<MX, MY, MZ, false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_pixel<MX, MY, MZ, false, false>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -148,6 +153,14 @@ int auto_tile_rows(int H, int W, int block_columns) {
   int ty = 32;
   while (ty > 1 && xb * ((H + ty - 1) / ty) < 2048) ty /= 2;
   return ty;
+}
+
+bool tiles_compute_rows(int mx, int H, int W, int TY, bool refined) {
+  if (refined) return false;
+  if (mx == 9) return true;
+  if (mx == 16) return TY >= 8;
+  const long long tiles = (long long)((W + Shape<8, 8, 4>::PPB - 1) / Shape<8, 8, 4>::PPB) * ((H + TY - 1) / TY);
+  return TY >= 32 || (TY == 1 && tiles <= 1024);
 }
 
 hipError_t launch_pixel(int mx, int my, int mz, const PixArgs& a, hipStream_t s) {

@@ -83,11 +83,6 @@ static __device__ __forceinline__ float2 dpp2(float2 v) { return f2(dppf<CTRL>(v
 // (lane j gets 15 - j), then rotated by one
 static __device__ __forceinline__ float2 row_neg(float2 v) { return dpp2<ROR1>(dpp2<MIRROR>(v)); }
 
-// The value is computed here, and memory accesses are not moved across (no
-// instruction): without it the compiler sinks a pass's arithmetic below the next
-// pass's loads and holds both in registers.
-static __device__ __forceinline__ void pass_done(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory"); }
-
 // Observer state of the 16x16x8 kernel, per pixel: [kz / 2][plane][ky] x
 // (kz even, kz odd) complex, so that one 16-byte load per lane covers 1 KB
 // of contiguous memory across the wavefront.  Float2 index of (plane, ky, kz):

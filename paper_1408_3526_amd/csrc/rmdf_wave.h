@@ -39,6 +39,11 @@ static __device__ __forceinline__ T& at(T* base, unsigned bytes) {
   return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
 }
 
+// The value is computed here, and memory accesses are not moved across (no
+// instruction): without it the compiler sinks a pass's arithmetic below the next
+// pass's loads and holds both in registers.
+static __device__ __forceinline__ void pass_done(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory"); }
+
 // Orders this wavefront's LDS accesses (lanes of one wavefront exchange
 // through LDS without a workgroup barrier).
 static __device__ __forceinline__ void wave_lds_sync() {

@@ -35,3 +35,46 @@ def test_generic_tile_remainders(orc, M, H, W, nx, ny, tile):
     r = orc.run(_cfg(orc, H, W, M, gx, gy), fr, want_rs=True)
     check_rs(g, r)
     check_velocity_and_output(g, r, fr, nx, gx, gy)
+
+
+@pytest.mark.parametrize("M,H,W,tile", [(M8, 70, 21, 64), (M8, 75, 30, 70), (M8, 9, 21, 1), (M9, 70, 19, 64),
+                                        (M9, 9, 21, 1), (M9, 34, 18, 33), (M16, 70, 17, 64), (M16, 41, 37, 8)])
+def test_rows_computed_in_tiles_equal_the_row_kernel(M, H, W, tile):
+    """Tiles that compute their own row spectra (single streams) against the row
+    kernel's (the batch uses it for every stream), bit for bit: tiles beyond the
+    32 rows staged at a time, columns past the frame, non-finite samples."""
+    from paper_1408_3526_amd import binding
+    rng = np.random.default_rng(H + W)
+    fr = (rng.normal(size=(10, H, W)) * 10 + 100).astype(np.float32)
+    fr[2, H // 2, W // 3] = np.nan
+    fr[5, 0, 0] = np.inf
+    fr[5, H - 1, W - 1] = -np.inf
+    g = scenes.grid(-2, 2, 0.5)
+    f = binding.Filter(H, W, *M, g, g, tile_rows=tile, kernel_variant=1)
+    b = binding.Batch([dict(H=H, W=W, M=M, gx=g, gy=g)], tile_rows=tile, kernel_variant=1)
+    dev = torch.from_numpy(fr).cuda()
+    for t in range(len(fr)):
+        f.push_frame(dev[t])
+        b.push([dev[t]])
+        out, vxy, idx = b.output(0)
+        assert torch.equal(f.output(), out), t
+        assert torch.equal(f.velocity()[1], idx), t
+    assert f.nonfinite_count() == 3
+    f.close()
+    b.close()
+
+
+@pytest.mark.parametrize("M", [M8, M9])
+def test_no_delay_reads_the_frame_being_stored(orc, M):
+    """Output delay 0 in time: the delayed sample is the current frame's, whose
+    delay-ring slot the same launch is storing (a non-finite sample reads as 0)."""
+    H, W, T = 12, 14, 8
+    rng = np.random.default_rng(3)
+    fr = (rng.normal(size=(T, H, W)) * 5 + 50).astype(np.float32)
+    fr[4, 3, 2] = np.nan
+    g = scenes.grid(-1, 1, 0.5)
+    r = run_gpu(fr, M, g, g, delay=(2, 3, 0), tile_rows=1)
+    o = orc.run(_cfg(orc, H, W, M, g, g, dx=2, dy=3, dt=0), fr, want_rs=True)
+    check_rs(r, o)
+    check_velocity_and_output(r, o, np.where(np.isfinite(fr), fr, 0), len(g), g, g)
+    assert r["nonfinite"] == 1
