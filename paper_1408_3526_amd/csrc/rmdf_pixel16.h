@@ -29,7 +29,8 @@
 // the modes that stream a whole observer state run two with the next row's state
 // loaded one row ahead (three without: 1.20 against 1.18 ms).  Against two
 // wavefronts with the prefetch throughout, four passes along kx and one candidate
-// per T read in stage C: ring 1.10 -> 0.84 ms, pairs 1.06 -> 0.89 ms a frame,
+// per T read in stage C: ring 1.10 -> 0.82 ms, pairs 1.06 -> 0.75 ms a frame
+// (the pairs' last 0.14 ms from loads that need no full wait and no spills),
 // refined 317x243 0.336 -> 0.297 ms, single frames 1.23 -> 1.17 ms.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -91,9 +92,11 @@ static __host__ __device__ __forceinline__ int st16_index(int p, int ky, int kz)
 }
 
 // Staged planes in LDS: index within a plane of the kz pair (2j, 2j + 1) of row
-// ky.  The four 16-byte pairs of a row are rotated by ky / 4, so that a row of
-// 16 lanes accessing one pair each covers all 64 banks.
-static __device__ __forceinline__ int sb_pair(int ky, int j) { return ky * MZ + (((j + (ky >> 2)) & 3) << 1); }
+// ky.  The four 16-byte pairs of a row are permuted by ky / 4, so that a row of
+// 16 lanes accessing one pair each covers all 64 banks; pair j of a row is pair
+// 0's index with 2j flipped (sb_flip), so a lane keeps one index per row.
+static __device__ __forceinline__ int sb_pair(int ky, int j) { return ky * MZ + ((j ^ (ky >> 2)) << 1); }
+static __device__ __forceinline__ int sb_flip(int pair0, int j) { return pair0 ^ (j << 1); }
 
 // w_8^k X for the eight posterior states (exact rotations for even k)
 static __device__ __forceinline__ float2 rot8(float2 a, int k) {
@@ -131,11 +134,11 @@ constexpr size_t SMEM16_DIRECT = SMEM16 + sizeof(float4) * WAVES * CRING + sizeo
 template <int MODE>
 constexpr size_t smem16_bytes() { return MODE == 5 ? SMEM16_DIRECT : SMEM16; }
 
-// One (ky) row of a staged plane, all kz; rp[j] = sb_pair(row, j).
-static __device__ __forceinline__ void ld_row(const lds_v2* plane, const int (&rp)[MZ / 2], float2 (&v)[MZ]) {
+// One (ky) row of a staged plane, all kz; rp = sb_pair(row, 0).
+static __device__ __forceinline__ void ld_row(const lds_v2* plane, int rp, float2 (&v)[MZ]) {
 #pragma unroll
   for (int j = 0; j < MZ / 2; ++j) {
-    const float4 q = ld4(plane + rp[j]);
+    const float4 q = ld4(plane + sb_flip(rp, j));
     v[2 * j] = f2(q.x, q.y);
     v[2 * j + 1] = f2(q.z, q.w);
   }
@@ -162,7 +165,7 @@ static __device__ __forceinline__ float hann_pow(float2 c, float2 l, float2 r) {
 // S(-1, ky, kz) = conj S(1, -ky, -kz), S(9, ky, kz) = conj S(7, -ky, -kz).
 template <bool LM, bool RM>
 static __device__ __forceinline__ float2 hann_x_power(const lds_v2* c, const lds_v2* l, const lds_v2* r,
-                                                      const int (&rp)[MZ / 2], const int (&mp)[MZ / 2], float (&P)[MZ]) {
+                                                      int rp, int mp, float (&P)[MZ]) {
   if (LM || RM) {
     float2 vl[MZ], vr[MZ], vc[MZ];
     ld_row(l, LM ? mp : rp, vl);
@@ -175,7 +178,8 @@ static __device__ __forceinline__ float2 hann_x_power(const lds_v2* c, const lds
   } else {
 #pragma unroll
     for (int j = 0; j < MZ / 2; ++j) {
-      const float4 vl = ld4(l + rp[j]), vr = ld4(r + rp[j]), vc = ld4(c + rp[j]);
+      const int at = sb_flip(rp, j);
+      const float4 vl = ld4(l + at), vr = ld4(r + at), vc = ld4(c + at);
       P[2 * j] = hann_pow(f2(vc.x, vc.y), f2(vl.x, vl.y), f2(vr.x, vr.y));
       P[2 * j + 1] = hann_pow(f2(vc.z, vc.w), f2(vl.z, vl.w), f2(vr.z, vr.w));
     }
@@ -327,12 +331,7 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
   // staging rows: this lane's ky and its mirror -ky; pair r of each for the
   // steps that spread a plane's four kz pairs over the four lane groups
   const int my = (MY - ky) & 15;
-  int rp[MZ / 2], mp[MZ / 2];
-#pragma unroll
-  for (int j = 0; j < MZ / 2; ++j) {
-    rp[j] = sb_pair(ky, j);
-    mp[j] = sb_pair(my, j);
-  }
+  const int rp0 = sb_pair(ky, 0), mp0 = sb_pair(my, 0);
   const int oj = sb_pair(ky, r);                                   // kz = 2r, 2r + 1
   const int m0 = sb_pair(my, (4 - r) & 3), m1 = sb_pair(my, 3 - r) + 1;   // row -ky, kz = -2r, -2r - 1
   // stage B: LB lanes per kx, lane g taking l_y = g, g + LB, ...
@@ -350,6 +349,17 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
   const int kyc = (ky <= 8) ? ky : ky - 16;
   // lattice background coefficients (table and spatial factors in LDS)
   const bool lattice = a.gtab != nullptr;
+  const float lat_s = (float)a.lat_q * (1.0f / 16.0f);
+  // A load whose value is needed at once waits for every load and store before
+  // it (vector memory completes in order), and so does any wait that follows a
+  // load under a condition.  The VALU-bound forms without a row prefetch
+  // therefore take the chosen velocity's lattice steps from LDS (ring 838 -> 820 us
+  // a 640x512 frame), and the pair form issues its loads unconditionally, so that a
+  // wait can count them (with the lattice steps 887 -> 852 us a frame).  The forms
+  // bound by the state stream lose by either (single frames 1162 us a frame, 1177
+  // and 1198): their waits hold back a wavefront's next loads until its stores
+  // have drained.
+  constexpr bool NO_WAIT = (MODE >= 4), COUNTED = (MODE == 6);
 
   // row spectra [y][x][plane]: element (row yy) at rsA[yy * rstride]
   const size_t rstride = (size_t)a.W * 8;
@@ -438,7 +448,11 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
   auto load_rows = [&](int y, const float2* rs, float2& na, float2& nb, float2& oa, float2& ob) {
     na = at(rs + (size_t)y * rstride, roA);
     nb = at(rs + (size_t)y * rstride, roB);
-    if (MODE != 5 && y >= MY) {
+    if (COUNTED) {                         // rows above the frame: dropped below
+      const int yo = max(y - MY, 0);
+      oa = at(rs + (size_t)yo * rstride, roA);
+      ob = at(rs + (size_t)yo * rstride, roB);
+    } else if (MODE != 5 && y >= MY) {
       oa = at(rs + (size_t)(y - MY) * rstride, roA);
       ob = at(rs + (size_t)(y - MY) * rstride, roB);
     }
@@ -477,6 +491,10 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
     auto frame = [&](auto fc) {
       constexpr int F = decltype(fc)::value;
       constexpr bool LAST = (MODE != 6) || (F == 1);
+      int rp = rp0, mp = mp0;
+      // as wC: the LDS places derived from these would otherwise be held across
+      // the pair's loop and spilled (a reload waits as above: 852 -> 785 us a frame)
+      if (MODE == 6) asm volatile("" : "+v"(rp), "+v"(mp));
       float2& cA = F ? acA2 : acA;
       float2& cB = F ? acB2 : acB;
       float2& cnA = F ? nA2 : nA;
@@ -500,6 +518,7 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
         }
       } else {
         // ---- column sliding DFT
+        if (COUNTED && y < MY) coA = coB = f2(0.f, 0.f);
         const float2 iA = f2(cnA.x - coA.x, cnA.y - coA.y), iB = f2(cnB.x - coB.x, cnB.y - coB.y);
         cA = f2(wy.x * cA.x - wy.y * cA.y + iA.x, wy.x * cA.y + wy.y * cA.x + iA.y);
         cB = f2(wy.x * cB.x - wy.y * cB.y + iB.x, wy.x * cB.y + wy.y * cB.x + iB.y);
@@ -575,15 +594,15 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       wave_lds_sync();                     // previous row's stage C reads are done
 #pragma unroll
       for (int j = 0; j < MZ / 2; ++j) {
-        st4(s_b + pA * SB_PLANE + rp[j], HA[2 * j].x, HA[2 * j].y, HA[2 * j + 1].x, HA[2 * j + 1].y);
-        st4(s_b + pB * SB_PLANE + rp[j], HB[2 * j].x, HB[2 * j].y, HB[2 * j + 1].x, HB[2 * j + 1].y);
+        st4(s_b + pA * SB_PLANE + sb_flip(rp, j), HA[2 * j].x, HA[2 * j].y, HA[2 * j + 1].x, HA[2 * j + 1].y);
+        st4(s_b + pB * SB_PLANE + sb_flip(rp, j), HB[2 * j].x, HB[2 * j].y, HB[2 * j + 1].x, HB[2 * j + 1].y);
       }
       if (MODE != 1 && MODE != 2 && r == 3) {
         // plane 9 = conj of plane 7 at (-ky, -kz)
 #pragma unroll
         for (int j = 0; j < MZ / 2; ++j) {
           const float2 h0 = HB[(MZ - 2 * j) & 7], h1 = HB[MZ - 1 - 2 * j];
-          st4(s_b + 9 * SB_PLANE + mp[j], h0.x, -h0.y, h1.x, -h1.y);
+          st4(s_b + 9 * SB_PLANE + sb_flip(mp, j), h0.x, -h0.y, h1.x, -h1.y);
         }
       }
       wave_lds_sync();
@@ -604,7 +623,11 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       // input sample
       float idel = 0.f;
       if (MODE != 2 && F == 0) {
-        if (two) {
+        if (COUNTED) {
+#pragma unroll
+          for (int j = 0; j < NC_IT; ++j)
+            rprev[j] = at(rq, 4u * (unsigned)min(wC + (two ? (j >> 1) * GC * nvx + (j & 1) * LC : 3 * j * nvx), nv - 1));
+        } else if (two) {
 #pragma unroll
           for (int j = 0; j < NC_IT - 1; ++j)
             rprev[j] = at(rq, 4u * (unsigned)min(wC + ((j >> 1) * GC * nvx + (j & 1) * LC), nv - 1));
@@ -615,12 +638,17 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       }
       {
         const int xs = x - a.dx, ys = y - a.dy;
-        if (rdel != nullptr && xs >= 0 && ys >= 0) idel = rdel[(size_t)ys * a.W + xs];
+        const bool ok = rdel != nullptr && xs >= 0 && ys >= 0;
+        if (COUNTED) {
+          const float v = *(ok ? rdel + (size_t)ys * a.W + xs : a.gx);
+          idel = ok ? v : 0.f;
+        } else if (ok) {
+          idel = rdel[(size_t)ys * a.W + xs];
+        }
       }
       // next row's state and row-spectrum samples (see the pipeline note);
       // issued after the loads above, which stage C waits for (vector memory
       // completes in order)
-      if (MODE == 6 && F == 0) load_rows(y, rs2, nA2, nB2, oA2, oB2);
       if (PREFETCH && y + 1 < y1) {
         if (F == 0) load_state(y + 1);
         load_rows(y + 1, F ? rs2 : rs1, cnA, cnB, coA, coB);
@@ -811,6 +839,9 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       };
       if (two) stage_c(std::integral_constant<int, 2>{});
       else stage_c(std::integral_constant<int, 1>{});
+      // the pair's second row samples: here rather than before stage C, where the
+      // registers they land in cost spills (785 against 749 us a frame)
+      if (MODE == 6 && F == 0) load_rows(y, rs2, nA2, nB2, oA2, oB2);
       group_amax<64>(bv, bi);
       const int istar = (bi < nv) ? bi : 0;
       if (MODE == 2 && lane == 0) a.fidx[pix] = istar;
@@ -836,7 +867,13 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
 
       // ---- background estimate with the chosen velocity's coefficients (the
       // posterior state is still in registers)
-      const int hsel = __builtin_amdgcn_readfirstlane((a.vmode == 2) ? nv : istar);
+      const int best = __builtin_amdgcn_readfirstlane(istar), iyb = (best * magic_nvx) >> 16;
+      const int hsel = (a.vmode == 2) ? nv : best;
+      auto grid_v = [&]() {
+        return (a.vmode == 2) ? f2(a.fvx, a.fvy) : f2(s_gx[best - iyb * nvx], s_gx[nvx + iyb]);
+      };
+      float2 vsel = f2(0.f, 0.f);
+      if (NO_WAIT) vsel = grid_v();
       float acc = 0.f;
       if (MODE == 3) {
         if (kyc >= -a.by && kyc <= a.by) {
@@ -845,8 +882,16 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
         }
       } else if (lattice) {
         // coefficient = E(kx, ky) G[(nx kx + ny ky) mod Q][kz]; sum_kz G X first
-        const int nq = a.latq[hsel];
-        const int nxv = nq >> 16, nyv = (int)(short)(nq & 0xffff);
+        int nxv, nyv;
+        if (NO_WAIT) {
+          // the velocity in lattice steps (exact: a whole number of 16 / lat_q)
+          nxv = (int)rintf(vsel.x * lat_s);
+          nyv = (int)rintf(vsel.y * lat_s);
+        } else {
+          const int nq = a.latq[hsel];
+          nxv = nq >> 16;
+          nyv = (int)(short)(nq & 0xffff);
+        }
         const int qm = a.lat_q - 1;
         const lds_v2* gA = s_g + ((nxv * pA + nyv * kyc) & qm) * GROW;
         const lds_v2* gB = s_g + ((nxv * pB + nyv * kyc) & qm) * GROW;
@@ -886,12 +931,12 @@ static __device__ __forceinline__ void pixel16_tile(const PixArgs& a, const floa
       } else if (lane == 0) {
         if (!isfinite(idel)) idel = 0.f;
         a.out[pix] = idel - acc;
+        if (!NO_WAIT) vsel = grid_v();
         if (a.vmode == 2) {
-          a.vxy[pix] = make_float2(a.fvx, a.fvy);
+          a.vxy[pix] = vsel;
           a.vidx[pix] = -1;
         } else {
-          const int best = __builtin_amdgcn_readfirstlane(istar), iyb = (best * magic_nvx) >> 16;
-          a.vxy[pix] = (MODE == 3) ? vref : make_float2(s_gx[best - iyb * nvx], s_gx[nvx + iyb]);
+          a.vxy[pix] = (MODE == 3) ? vref : vsel;
           a.vidx[pix] = istar;
         }
       }

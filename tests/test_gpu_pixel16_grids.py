@@ -94,3 +94,26 @@ def test_refined_grids(nx, ny):
         well = inner & (-den >= 1e-3 * np.abs(r1))
         v = g[i] - 0.5 * 0.25 * (r2 - r0) / np.where(den == 0, 1, den)
         assert np.abs(vxy[..., axis] - v)[well].max(initial=0) <= 1e-3 * 0.25
+
+
+@pytest.mark.parametrize("step,shift", [(1.0, 0.0), (0.5, 8.0), (0.25, -3.75), (0.3, 0.0), (1.0, 100.0)])
+def test_pairs_and_ring_lattice_steps(orc, step, shift):
+    """The chosen velocity in lattice steps: single frames read them from a
+    table, pairs and the ring form them from the grid (all lattice scales, a
+    grid off the lattice, velocities beyond one turn of the table)."""
+    fr, _, _ = _frames(9, 5)
+    gx = ((np.arange(9) - 4) * step + shift).astype(np.float32)
+    gy = ((np.arange(5) - 2) * step - shift).astype(np.float32)
+    T, H, W = fr.shape
+    dev = torch.from_numpy(fr).cuda()
+    a, b = (binding.Filter(H, W, *M, gx, gy, tile_rows=5) for _ in range(2))
+    outs = [torch.empty(H, W, device="cuda") for _ in range(T)]
+    for t in range(T):
+        a.push_frame(dev[t])
+    b.push_frames(list(dev), outs)
+    assert torch.equal(a.output(), outs[-1])
+    assert torch.equal(a.velocity()[0], b.velocity()[0])
+    ring = run_gpu(fr, M, gx, gy, tile_rows=5, temporal=binding.TEMPORAL_RING)
+    _check(ring, orc.run(_cfg(orc, H, W, M, gx, gy), fr, want_rs=True), fr, 9, gx, gy)
+    a.close()
+    b.close()
