@@ -168,11 +168,12 @@ static __device__ void row_chunk(const float* __restrict__ f, float2* __restrict
 // instead of one per 64 candidates), and the planes beyond the half spectrum
 // are stored as mirrors so that the Hann pass along kx reads fixed offsets.
 // Against the form with workgroup barriers and loads in the candidate loop
-// (us per frame, output and velocity read): 9x9x5 640x512 941 -> 505 (VALU 69%
-// busy, 659 instructions an anchor; the state and R traffic alone would take
-// 370), 8x8x4 640x512 397 -> 240, 16x16x8 319x241 with 33x33 candidates
-// 1243 -> 630, the paper's 64x64 frames 24.4 -> 19.4 (the row spectra computed in
-// the tiles are 16, 0, 10 and 1.8 of these).
+// (us per frame, output and velocity read): 9x9x5 640x512 941 -> 470 (4.25 TB/s of
+// cache-line traffic; the state and R alone would take 370 at the copy rate), 8x8x4
+// 640x512 397 -> 217, 16x16x8 319x241 with 33x33 candidates 1243 -> 537 (3.7 TB/s,
+// two wavefronts per SIMD; 391), the paper's 64x64 frames 24.4 -> 18.2.  Of these, row
+// spectra computed in the tiles give 16, 0, 10 and 1.8, and the state moved in
+// contiguous runs, non-temporal, 32, 22, 93 and 1.1.
 template <int MX, int MY, int MZ>
 struct Shape {
   static constexpr bool EVEN = (MX % 2 == 0);
@@ -194,11 +195,15 @@ struct Shape {
   static constexpr int QT_ELEMS = NXH * MYQ + NVY_MAX * NXT;
   static constexpr int W_ELEMS = PPW * (S_ELEMS > QT_ELEMS ? S_ELEMS : QT_ELEMS);   // per wavefront
   static constexpr int MXQ = (MX + 1) / 2 * 2;
-  static constexpr int TAB_ELEMS = NVY_MAX * MYT + NVX_MAX * NXT + MYQ + MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;
+  // one column per lane: where the operands of each candidate lie; whole rounds (and
+  // whole groups of NB rounds)
+  static constexpr int NB = 6;                              // candidates per lane whose smoothed R is loaded together
+  static constexpr int WC = CPL > 1 ? 0 : (NVX_MAX * NVY_MAX + NB * LPP - 1) / (NB * LPP) * (NB * LPP) + LPP;
+  static constexpr int TAB_ELEMS = NVY_MAX * MYT + NVX_MAX * NXT + MYQ + MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2 + WC / 2;
   // row spectra of SR rows and the My above them for the workgroup's anchors;
   // the samples they come from (one resonator segment and the Mx before it)
   // lie in the wavefronts' staging area while it is idle
-  static constexpr int SR = 32;
+  static constexpr int SR = PPW == 2 ? 24 : 32;             // (8x8x4: four workgroups' LDS on a CU)
   static constexpr int RS_ELEMS = ((SR + MY) * PPB * NP + 1) / 2 * 2;
   static constexpr int SW = MX + RSEG + (MX % 2 ? 3 : 4);   // floats per sample row: 16-byte aligned, spread over banks
   static_assert((SR + MY) * SW <= 2 * WAVES * W_ELEMS, "samples fit the staging area");
@@ -334,9 +339,8 @@ template <int MX, int MY, int MZ, bool REFINED = false, bool OWN_ROWS = false>
 static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float* ring_delayed, int xb, int yb, char* smem) {
   using SH = Shape<MX, MY, MZ>;
   constexpr int NP = SH::NP, NXH = SH::NXH, NCOL = SH::NCOL, LPP = SH::LPP, CPL = SH::CPL, PPW = SH::PPW;
-  constexpr int MZP = SH::MZP, MYQ = SH::MYQ, MYT = SH::MYT, NXT = SH::NXT;
+  constexpr int MZP = SH::MZP, MYQ = SH::MYQ, MYT = SH::MYT, NXT = SH::NXT, NB = SH::NB;
   constexpr bool EVEN = SH::EVEN;
-
   lds_v2* s_tauy = (lds_v2*)smem;                // [nvy][MYT]
   lds_v2* s_taux = s_tauy + NVY_MAX * MYT;       // [nvx][NXT]
   lds_v2* s_twy = s_taux + NVX_MAX * NXT;        // [MY]
@@ -346,7 +350,8 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   const int cl = (PPW == 1) ? lane : lane % LPP;           // lane within the anchor
   lds_v2* s_twx = s_twy + MYQ;                   // [MX]
   lds_float* s_gx = (lds_float*)(s_twx + SH::MXQ);   // [nvx], then gy [nvy]
-  lds_v2* s_rs = s_twx + SH::MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2;   // [SR + MY][PPB][NP]
+  lds_u32* s_itC = (lds_u32*)(s_twx + SH::MXQ + (NVX_MAX + NVY_MAX + 3) / 4 * 2);   // [WC] candidates
+  lds_v2* s_rs = (lds_v2*)(s_itC + SH::WC);      // [SR + MY][PPB][NP]
   lds_v2* s_w0 = s_rs + (OWN_ROWS ? SH::RS_ELEMS : 0);
   lds_v2* s_w = s_w0 + wv * SH::W_ELEMS + ps * (SH::W_ELEMS / PPW);
   const int nvx = a.nvx, nvy = a.nvy, nv = a.nv;
@@ -355,6 +360,15 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   for (int i = tid; i < nvx * NXH; i += 256) s_taux[i / NXH * NXT + i % NXH] = v2f{a.taux[i].x, a.taux[i].y};
   for (int i = tid; i < MX; i += 256) s_twx[i] = v2f{a.twx[i].x, a.twx[i].y};
   for (int i = tid; i < nvx + nvy; i += 256) s_gx[i] = (i < nvx) ? a.gx[i] : a.gy[i - nvx];
+  if (CPL == 1) {
+    // byte offsets of candidate (iy, ix): T row, weight row (places past the grid
+    // repeat the last one)
+    const float inv_x = 1.0f / (float)nvx;
+    for (int i = tid; i < (nv + LPP - 1) / LPP * LPP + LPP; i += 256) {
+      const int w = min(i, nv - 1), iy = (int)(((float)w + 0.5f) * inv_x), ix = w - iy * nvx;
+      s_itC[i] = (unsigned)(iy * NXT * 8) | (unsigned)(ix * NXT * 8) << 16;
+    }
+  }
 
   const int y0 = yb * a.TY;
   const int y1 = min(a.H, y0 + a.TY);
@@ -377,18 +391,31 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     ky[j] = col[j] % MY;
   }
   // addresses: a base per row (the same in all lanes) and a 32-bit offset per lane
-  unsigned so[CPL];
   unsigned ro[CPL];
   const lds_v2* rs_own[CPL];                     // this column's row spectrum, row 0 of s_rs
 #pragma unroll
   for (int j = 0; j < CPL; ++j) {
-    so[j] = (unsigned)((dxw * NCOL + col[j]) * MZ) * 8u;
     ro[j] = (unsigned)(dxw * NP + p[j]) * 8u;
     rs_own[j] = s_rs + (wv * PPW + dxw) * NP + p[j];
   }
   constexpr int RSR = SH::PPB * NP;              // s_rs row
   const unsigned qo = (unsigned)(dxw * nv) * 4u;
-  const bool st_ok = px_ok && cl < NCOL;         // (CPL > 1: every lane's columns exist)
+  // The state in memory is [plane][ky][kz], a column's kz values side by side: a
+  // lane's own column would make accesses of 16 bytes at strides of 32 to 64, each
+  // touching every line of the anchor's run (9x9x5 640x512: 119 cache write requests
+  // an anchor, 61 when contiguous; 505 -> 475 us).  So the state moves between memory
+  // and LDS in contiguous runs, one piece of VL values per lane, and between LDS and
+  // registers by column.
+  constexpr int VL = (MZ % 2 == 0) ? 2 : 1;      // float2 per piece
+  constexpr int CS = (MZ % 2 == 0) ? MZP : MZ;   // column stride in LDS (padded: distinct banks)
+  constexpr int NPC = NCOL * MZ / VL, NL = (NPC + LPP - 1) / LPP;   // pieces per anchor and lane
+  // (pieces past the last: the descriptors of load_row and of the stores end with
+  // the anchors' states, and in LDS they lie within the staging area)
+  static_assert(NL * LPP * VL <= SH::W_ELEMS / PPW && (PPW == 1 || NPC % LPP == 0), "pieces past the last");
+  const unsigned po = (unsigned)((dxw * NPC + cl) * VL) * 8u;
+  const int pl = (MZ % 2 == 0) ? cl * VL / MZ * CS + cl * VL % MZ : cl;
+  constexpr int PLS = (MZ % 2 == 0) ? LPP * VL / MZ * CS : LPP;   // LDS distance of a lane's pieces
+  const unsigned st_bytes = (unsigned)(NCOL * MZ * 8 * (PPW == 1 ? 1 : min(PPW, max(a.W - xw, 0))));
 
   // Staged planes: (kx in [-1, NXH], ky, kz) at s_w[((kx + 1) * MY + ky) * MZP + kz]
   auto sidx = [](int kx, int kyy) { return ((kx + 1) * MY + kyy) * MZP; };
@@ -437,17 +464,16 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   }
 
   // first row's state (and row spectra); later rows' are loaded one row ahead
-  float2 Xn[CPL][MZ], in_n[CPL], in_o[CPL];
+  float2 Xn[NL][VL], in_n[CPL], in_o[CPL];
   auto load_row = [&](int y) {
-    const float2* src = a.st + ((size_t)y * a.W + xw) * (NCOL * MZ);
+    const auto src = buffer_of(a.st + ((size_t)y * a.W + xw) * (NCOL * MZ), st_bytes);
     const float2* rn = a.rs + ((size_t)y * a.W + xw) * NP;
     const float2* rl = a.rs + ((size_t)max(y - MY, 0) * a.W + xw) * NP;
 #pragma unroll
-    for (int j = 0; j < CPL; ++j) {
-      const float2* s = &at(src, so[j]);         // (one address: the loads merge to 16 bytes)
+    for (int i = 0; i < NL; ++i) buffer_ld(src, po + 8u * VL * LPP * i, Xn[i]);
+    if (!OWN_ROWS) {
 #pragma unroll
-      for (int k = 0; k < MZ; ++k) Xn[j][k] = s[k];
-      if (!OWN_ROWS) {
+      for (int j = 0; j < CPL; ++j) {
         in_n[j] = at(rn, ro[j]);
         in_o[j] = at(rl, ro[j]);
       }
@@ -455,25 +481,21 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   };
   if (active) load_row(y0);
 
-  // The lane's place in stages B (item kx * nvy + iy) and C (item iy * nvx + ix).
-  // One column per lane: items cl, cl + LPP, ..., the pair of indices moving by
-  // (LPP / n, LPP % n) with a carry.  Two columns per lane (MX = 16): a weight or
-  // T row is 128 or 72 bytes, and the LDS return path, not the FMAs, bounds
-  // stages that read two rows per item; so LB lanes per kx share a Q row over
-  // the l_y they take (g, g + LB, ...), and a T row serves KX = 3 candidates of
-  // one l_y, LC = ceil(nvx / 3) apart, G l_y at a time (319x241, 33x33
-  // candidates: 733 against 890 us a frame; the small windows' flat order is
-  // 8 to 10% faster than this one).
+  // Stages B (item kx * nvy + iy) and C (item iy * nvx + ix).  B: LB lanes per kx share
+  // its Q row over the l_y they take (g, g + LB, ...).  C, one column per lane: items cl,
+  // cl + LPP, ..., whose operands' places are read from a table (the indices carried
+  // along took 15 of a candidate's 40 instructions; a lane that keeps one l_x and
+  // its weights is slower, 500 against 481 us for 9x9x5 640x512: its rows wait for each
+  // other).  C, two columns per lane (MX = 16): the LDS return path bounds a stage that
+  // reads two rows per item, so a T row serves KX = 3 candidates of one l_y, LC =
+  // ceil(nvx / 3) apart, G l_y at a time (319x241, 33x33 candidates: 733 against 890 us
+  // a frame; the small windows are 8 to 10% faster in the flat order).
   constexpr bool ROWS = CPL > 1;
   constexpr int LB = LPP / NXH, KX = 3;
-  const int kxB = ROWS ? cl / LB : cl / nvy, iyB = ROWS ? cl - kxB * LB : cl - kxB * nvy;
-  const int dkB = LPP / nvy, diB = LPP - dkB * nvy;
-  const int LC = ROWS ? (nvx + KX - 1) / KX : nvx, G = LPP / LC;
+  const int kxB = cl / LB, iyB = cl - kxB * LB;
+  const int LC = (nvx + KX - 1) / KX, G = LPP / LC;
   const int iyC0 = cl / LC, ixC0 = cl - iyC0 * LC;
-  const int dxC = LPP - G * LC;                  // (one column per lane)
-  const int o_q = kxB * MYQ, o_ty = iyB * MYT, o_t = iyB * NXT + kxB, o_tC = iyC0 * NXT, o_xC = ixC0 * NXT;
-  const int t_last = (nvy - 1) * NXT;
-  constexpr int NB = 6;                          // candidates per lane whose smoothed R is loaded together
+  const int o_q = kxB * MYQ, o_ty = iyB * MYT, o_t = iyB * NXT + kxB;
   const float inv_nvx = 1.0f / (float)nvx;
 
   for (int yc = y0; yc < y1; yc += SH::SR) {      // OWN_ROWS: SR rows of row spectra at a time
@@ -498,19 +520,29 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     const int r0 = (y - yc) * RSR;
     // opaque per row: what stage C derives from the lane's place is computed again each
     // row instead of being held in registers (or spilled) across the loop
-    int iyC = iyC0, ixC = ixC0, wC = cl;
+    int iyC = iyC0, ixC = ixC0;
     if (ROWS) asm volatile("" : "+v"(iyC), "+v"(ixC));
-    else asm volatile("" : "+v"(wC));
     float2 X[CPL][MZ];
     float* rp = a.rsm + pix0 * nv;
     float rn[NB];
-    // smoothed R of the next NB candidates: from item w on, or (ROWS) NB / KX
-    // rounds from l_y = w on; places past the grid read its last value
+    // smoothed R of the next NB candidates: (ROWS) NB / KX rounds from l_y = w on,
+    // places past the grid reading its last value; else from item w on, through a
+    // buffer descriptor of the anchors' values (reads past it give 0)
+    const auto rb = buffer_of(rp, 4u * (unsigned)(nv * (PPW == 1 ? 1 : min(PPW, a.W - xw))));
     auto load_r = [&](int w) {
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
-        rn[i] = at(rp, qo + 4u * (unsigned)min(ROWS ? (w + i / KX * G) * nvx + ixC + i % KX * LC : w + i * LPP, nv - 1));
+      for (int i = 0; i < NB; ++i) {
+        if (ROWS) rn[i] = at(rp, qo + 4u * (unsigned)min((w + i / KX * G) * nvx + ixC + i % KX * LC, nv - 1));
+        else rn[i] = buffer_ld(rb, qo + 4u * (unsigned)(w + cl) + 4u * LPP * i);
+      }
     };
+    wave_lds_sync();                             // the previous row's stage C reads are done
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      if constexpr (VL == 2) st4(s_w + pl + i * PLS, Xn[i][0].x, Xn[i][0].y, Xn[i][1].x, Xn[i][1].y);
+      else st2(s_w + pl + i * PLS, Xn[i][0]);
+    }
+    wave_lds_sync();
 #pragma unroll
     for (int j = 0; j < CPL; ++j) {
       // ---- column sliding DFT: comb on the row spectra, resonator w_y^ky
@@ -521,24 +553,49 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
       // ---- temporal deadbeat observer: prior = rotate(posterior), innovation
       // e = input - sum(prior), posterior = prior + e / Mz
       float2 sum = make_float2(0.f, 0.f);
+      float2 post[MZ];
+      if constexpr (MZ % 2 == 0) {
+        ld_col<MZ>(s_w + col[j] * CS, post);
+      } else {
+#pragma unroll
+        for (int k = 0; k < MZ; ++k) post[k] = ld2(s_w + col[j] * CS + k);
+      }
 #pragma unroll
       for (int k = 0; k < MZ; ++k) {
-        X[j][k] = cmul(twz[k], Xn[j][k]);
+        X[j][k] = cmul(twz[k], post[k]);
         sum = cadd(sum, X[j][k]);
       }
       const float2 e = cscale(csub(s2, sum), 1.0f / MZ);
 #pragma unroll
       for (int k = 0; k < MZ; ++k) X[j][k] = cadd(X[j][k], e);
-      if (st_ok) {
-        float2* dst = &at(a.st + pix0 * (NCOL * MZ), so[j]);
+      if constexpr (MZ % 2 == 0) {
+        st_col<MZ>(s_w + col[j] * CS, X[j]);
+      } else {
 #pragma unroll
-        for (int k = 0; k < MZ; ++k) dst[k] = X[j][k];
+        for (int k = 0; k < MZ; ++k) st2(s_w + col[j] * CS + k, X[j][k]);
       }
+    }
+    wave_lds_sync();
+    {
+      const auto dst = buffer_of(a.st + pix0 * (NCOL * MZ), st_bytes);
+      float2 v[NL][VL];
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        if constexpr (VL == 2) {
+          const float4 q = ld4(s_w + pl + i * PLS);
+          v[i][0] = make_float2(q.x, q.y);
+          v[i][1] = make_float2(q.z, q.w);
+        } else {
+          v[i][0] = ld2(s_w + pl + i * PLS);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NL; ++i) buffer_st(dst, v[i], po + 8u * VL * LPP * i);
     }
     // this row's smoothed R (first rounds of stage C), the delayed sample and
     // the next row's state are in flight during the flow stages; stage C waits
     // for the first group only (vector memory completes in order)
-    load_r(ROWS ? iyC : wC);
+    load_r(ROWS ? iyC : 0);
     float idel = 0.f;
     {
       const int xs = x - a.dx, ys = y - a.dy;
@@ -555,13 +612,16 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
       float2 V[MZ];
 #pragma unroll
       for (int k = 0; k < MZ; ++k) V[k] = X[j][k];
-      if (col[j] == 0) {
+      if (!EVEN) {
+#pragma unroll
+        for (int k = 0; k < MZ; ++k) V[k] = make_float2(col[j] == 0 ? 0.f : X[j][k].x, col[j] == 0 ? 0.f : X[j][k].y);
+      } else if (col[j] == 0) {
 #pragma unroll
         for (int k = 0; k < MZ; ++k) {
-          // even Mx: the packed plane holds S(0) + j S(Mx/2); remove the S(0)
-          // part only: S(0)(0, kz) = (C(kz) + conj C(-kz)) / 2
+          // the packed plane holds S(0) + j S(Mx/2); remove the S(0) part only:
+          // S(0)(0, kz) = (C(kz) + conj C(-kz)) / 2
           const float2 cm = X[j][(MZ - k) % MZ];
-          V[k] = EVEN ? make_float2(0.5f * (X[j][k].x - cm.x), 0.5f * (X[j][k].y + cm.y)) : make_float2(0.f, 0.f);
+          V[k] = make_float2(0.5f * (X[j][k].x - cm.x), 0.5f * (X[j][k].y + cm.y));
         }
       }
 #pragma unroll
@@ -582,7 +642,7 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
           const float2 r = make_float2(dppf<ROR15>(v.x), dppf<ROR15>(v.y));
           Hy[j][k] = make_float2(2.f * v.x - l.x - r.x, 2.f * v.y - l.y - r.y);
         }
-      wave_lds_sync();                           // the previous row's stage C reads are done
+      wave_lds_sync();                           // the state's pieces are read
     } else {
       wave_lds_sync();
       st_col<MZ>(s_w + sidx(p[0], ky[0]), Hy[0]);
@@ -681,28 +741,9 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
       // issue slots)
       const lds_v2 *p_q = s_q + o_q, *p_ty = s_tauy + o_ty;
       lds_v2* p_t = s_t + o_t;
-      int kx = kxB, iy = iyB;
-      if (ROWS) {
-        if (kx < NXH) {
-          ld_col<MY>(p_q, q);
-          for (; iy < nvy; iy += LB, p_ty += LB * MYT, p_t += LB * NXT) item(p_ty, p_t);
-        }
-      } else {
-        while (kx < NXH) {
-          ld_col<MY>(p_q, q);
-          item(p_ty, p_t);
-          kx += dkB;
-          iy += diB;
-          p_q += dkB * MYQ;
-          p_ty += diB * MYT;
-          p_t += dkB + diB * NXT;
-          const int carry = (iy >= nvy) ? -1 : 0;
-          iy -= carry & nvy;
-          kx -= carry;
-          p_q += carry & MYQ;
-          p_ty -= carry & (nvy * MYT);
-          p_t += carry & (1 - nvy * NXT);
-        }
+      if (kxB < NXH) {
+        ld_col<MY>(p_q, q);
+        for (int iy = iyB; iy < nvy; iy += LB, p_ty += LB * MYT, p_t += LB * NXT) item(p_ty, p_t);
       }
     }
     wave_lds_sync();
@@ -713,24 +754,19 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     int bi = 0x7fffffff;
     {
       float2 t[NXH], tx[ROWS ? KX : 1][NXH];
-      auto item = [&](const float2 (&w_x)[NXH], float r_prev, int w) {
+      auto smooth = [&](const float2 (&w_x)[NXH], float r_prev) {
         float r = 0.f;
 #pragma unroll
         for (int kx = 0; kx < NXH; ++kx) r += t[kx].x * w_x[kx].x - t[kx].y * w_x[kx].y;
-        const float sm = (1.f - a.alpha) * r + a.alpha * r_prev;
-        if (px_ok) at(rp, qo + 4u * (unsigned)w) = sm;
-        amax_merge(bv, bi, sm, w);
-      };
-      float rc[NB];
-      auto next = [&]() {
-#pragma unroll
-        for (int i = 0; i < NB; ++i) rc[i] = rn[i];
+        return (1.f - a.alpha) * r + a.alpha * r_prev;
       };
       if constexpr (ROWS) {
+        float rc[NB];
 #pragma unroll
         for (int u = 0; u < KX; ++u) ld_col<NXH>(s_taux + min(ixC + u * LC, nvx - 1) * NXT, tx[u]);
         for (int iy0 = 0; iy0 < nvy; iy0 += NB / KX * G) {
-          next();
+#pragma unroll
+          for (int i = 0; i < NB; ++i) rc[i] = rn[i];
           if (iy0 + NB / KX * G < nvy) load_r(iy0 + NB / KX * G + iyC);
 #pragma unroll
           for (int v = 0; v < NB / KX; ++v) {
@@ -739,36 +775,64 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
               ld_col<NXH>(s_t + iy * NXT, t);
 #pragma unroll
               for (int u = 0; u < KX; ++u)
-                if (ixC + u * LC < nvx) item(tx[u], rc[v * KX + u], iy * nvx + ixC + u * LC);
+                if (ixC + u * LC < nvx) {
+                  const int w = iy * nvx + ixC + u * LC;
+                  const float sm = smooth(tx[u], rc[v * KX + u]);
+                  if (px_ok) at(rp, qo + 4u * (unsigned)w) = sm;
+                  amax_merge(bv, bi, sm, w);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);   // one round's LDS reads in flight at a time
           }
         }
       } else {
-        int ix = ixC, o_t = o_tC;
-        const lds_v2* p_x = s_taux + o_xC;
-        for (int w0 = 0; w0 < nv; w0 += NB * LPP) {
-          next();
-          if (w0 + NB * LPP < nv) load_r(w0 + NB * LPP + wC);
+        // A lane's candidates come in rising order, so only a larger value takes
+        // over, and the round it came in is all that is kept (a grid without a value
+        // above -infinity: below).  Whole groups have no lane past the grid.
+        int br = -1;
+        unsigned vo = qo + 4u * (unsigned)cl;
+        const lds_u32* it = s_itC + cl;
+        unsigned itC = it[0];
+        auto round = [&](int i, int rnd, bool ok, bool whole) {
+          const unsigned o = itC;
+          itC = it[(i + 1) * LPP];
+          ld_col<NXH>(lds_at(s_t, o & 0xffffu), t);
+          ld_col<NXH>(lds_at(s_taux, o >> 16), tx[0]);
+          const float sm = smooth(tx[0], rn[i]);
+          // (one anchor: the descriptor ends with its values)
+          buffer_st(rb, sm, (PPW == 1 || whole || ok ? vo : BUFFER_NONE) + 4u * LPP * i);
+          const bool take = (sm > bv) & (whole | ok);
+          bv = take ? sm : bv;
+          br = take ? rnd : br;
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        int w0 = 0, rnd = 0;
+        for (; w0 + NB * LPP < nv; w0 += NB * LPP, rnd += NB) {
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
-            if (w0 + i * LPP < nv) {             // uniform: some lane has a candidate
-              ld_col<NXH>(s_t + min(o_t, t_last), t);
-              ld_col<NXH>(p_x, tx[0]);
-              const int w = w0 + i * LPP + wC;
-              if (w < nv) item(tx[0], rc[i], w);
-              ix += dxC;
-              const int carry = (ix >= nvx) ? -1 : 0;
-              ix -= carry & nvx;
-              o_t += G * NXT + (carry & NXT);
-              p_x += dxC * NXT - (carry & (nvx * NXT));
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            round(i, rnd + i, true, true);
+            rn[i] = buffer_ld(rb, vo + 4u * LPP * (NB + i));
           }
+          vo += 4u * LPP * NB;
+          it += LPP * NB;
         }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          if (w0 + i * LPP < nv) round(i, rnd + i, cl < nv - w0 - i * LPP, false);   // uniform
+        bi = br < 0 ? 0x7fffffff : br * LPP + cl;
       }
     }
     group_amax<LPP>(bv, bi);
+    if (!ROWS && __any(bv == -INFINITY)) {       // overflowed: the first candidate of -infinity, if one is
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      int first = 0x7fffffff;
+      for (int w = cl; w < nv; w += LPP)
+        if (at(rp, qo + 4u * (unsigned)w) == -INFINITY) first = min(first, w);
+      first = group_ext<LPP, false>(first);
+      if (bv == -INFINITY) bi = first;
+    }
     const int istar = (bi < nv) ? bi : 0;   // no finite candidate: fall back to index 0
 
     // ---- velocity mode 3: refine the peak between grid points, from the

@@ -18,6 +18,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef RMDF_LDS v2f lds_v2;
 typedef RMDF_LDS v4f lds_v4;
 typedef RMDF_LDS float lds_float;
+typedef RMDF_LDS unsigned int lds_u32;
 __device__ __forceinline__ float2 ld2(const lds_v2* p) { const v2f v = *p; return make_float2(v.x, v.y); }
 __device__ __forceinline__ float4 ld4(const lds_v2* p) {
   const v4f v = *reinterpret_cast<const lds_v4*>(p);
@@ -38,6 +39,48 @@ template <class T>
 static __device__ __forceinline__ T& at(T* base, unsigned bytes) {
   return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
 }
+
+// Element at a byte offset from an LDS address
+static __device__ __forceinline__ lds_v2* lds_at(lds_v2* base, unsigned bytes) {
+  return (lds_v2*)((RMDF_LDS char*)base + bytes);
+}
+
+// Buffer descriptor of `bytes` bytes at p (the same in all lanes).  Reads past it
+// give 0 and writes past it are dropped, so lanes past the end of a run need
+// neither a mask nor a clamped index; BUFFER_NONE (with a small constant added)
+// lies past every run.  Word 3: untyped 32-bit data.
+typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
+static __device__ __forceinline__ buffer_rsrc buffer_of(void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)bytes, 0x00027000);
+}
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+static __device__ __forceinline__ float uf(unsigned v) { return __int_as_float((int)v); }
+static __device__ __forceinline__ unsigned fu(float v) { return (unsigned)__float_as_int(v); }
+static __device__ __forceinline__ float buffer_ld(buffer_rsrc b, unsigned off) {
+  return uf(__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+}
+static __device__ __forceinline__ void buffer_st(buffer_rsrc b, float v, unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b32(fu(v), b, (int)off, 0, 0);
+}
+// (8 and 16 bytes: the observer state, streamed once per frame; non-temporal, which
+// took 2 to 4% off a frame)
+constexpr int BUFFER_NT = 2;
+static __device__ __forceinline__ void buffer_ld(buffer_rsrc b, unsigned off, float2 (&v)[1]) {
+  const v2u q = __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, BUFFER_NT);
+  v[0] = make_float2(uf(q.x), uf(q.y));
+}
+static __device__ __forceinline__ void buffer_ld(buffer_rsrc b, unsigned off, float2 (&v)[2]) {
+  const v4u q = __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, BUFFER_NT);
+  v[0] = make_float2(uf(q.x), uf(q.y));
+  v[1] = make_float2(uf(q.z), uf(q.w));
+}
+static __device__ __forceinline__ void buffer_st(buffer_rsrc b, const float2 (&v)[1], unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b64(v2u{fu(v[0].x), fu(v[0].y)}, b, (int)off, 0, BUFFER_NT);
+}
+static __device__ __forceinline__ void buffer_st(buffer_rsrc b, const float2 (&v)[2], unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b128(v4u{fu(v[0].x), fu(v[0].y), fu(v[1].x), fu(v[1].y)}, b, (int)off, 0, BUFFER_NT);
+}
+constexpr unsigned BUFFER_NONE = 0x40000000u;
 
 // The value is computed here, and memory accesses are not moved across (no
 // instruction): without it the compiler sinks a pass's arithmetic below the next

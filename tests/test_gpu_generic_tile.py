@@ -78,3 +78,32 @@ def test_no_delay_reads_the_frame_being_stored(orc, M):
     check_rs(r, o)
     check_velocity_and_output(r, o, np.where(np.isfinite(fr), fr, 0), len(g), g, g)
     assert r["nonfinite"] == 1
+
+
+@pytest.mark.parametrize("M,nx,ny", [(M8, 9, 7), (M9, 13, 11), (M16, 13, 11)])
+def test_best_candidate_where_r_overflows(M, nx, ny):
+    """Samples whose power overflows FP32 in some anchors: the index is the first
+    of the largest smoothed R, values that are not numbers left out, and 0 where
+    there is no other."""
+    from paper_1408_3526_amd import binding
+    H, W, T = 13, 23, 5
+    rng = np.random.default_rng(nx)
+    fr = rng.normal(size=(T, H, W)) * 10.0 ** np.linspace(16, 20, W)
+    fr[:, :3] = 0.0
+    gx, gy = (((np.arange(n) - n // 2) * 0.25).astype(np.float32) for n in (nx, ny))
+    f = binding.Filter(H, W, *M, gx, gy, tile_rows=4, kernel_variant=1)
+    dev = torch.from_numpy(fr.astype(np.float32)).cuda()
+    seen = set()
+    for t in range(T):
+        f.push_frame(dev[t])
+        rs = f.smoothed_r().cpu().numpy()
+        idx = f.velocity()[1].cpu().numpy()
+        for y in range(H):
+            for x in range(W):
+                r = rs[y, x]
+                ok = r[~np.isnan(r)]
+                want = int(np.argmax(r == ok.max())) if ok.size else 0
+                assert idx[y, x] == want, (t, y, x)
+                seen.add("none" if not ok.size else "least" if np.isneginf(ok.max()) else "inf" if np.isinf(ok.max()) else "finite")
+    assert "finite" in seen and len(seen) > 1
+    f.close()
