@@ -70,3 +70,15 @@ def test_cfar_arguments():
         with pytest.raises(b.RmdfError) as e:
             b.cfar(x, guard, train, k)
         assert e.value.status == b.RMDF_E_INVAL
+
+
+@pytest.mark.parametrize("H,W,guard,train", [(507, 655, 4, 12), (509, 641, 0, 16), (1025, 1217, 1, 2), (1030, 1281, 1, 9),
+                                             (3, 65, 0, 1), (7, 63, 1, 1), (6, 129, 0, 15), (9, 64, 2, 5)])
+def test_cfar_tiles_of_either_height(H, W, guard, train):
+    """Frames on both sides of the choice between tiles of 16 and of 4 rows,
+    with staged rows that leave every remainder of a wavefront's rows."""
+    rng = np.random.default_rng(H + W + train)
+    x = rng.normal(size=(H, W)) * 2.0 + 0.3
+    for _ in range(max(1, H * W // 500)):
+        x[rng.integers(0, H), rng.integers(0, W)] += rng.uniform(8, 20) * rng.choice([-1, 1])
+    check(x, guard, train, 3.0)
