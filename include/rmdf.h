@@ -174,7 +174,7 @@ rmdf_status rmdf_push_frames(rmdf_ctx *ctx, int n, const float *const *frames_de
  * (-1 where a fixed velocity was used); either may be NULL.
  * Paper: v = l / l_z at the maximum of the smoothed autocorrelation on the
  * l_z = 1 slice (Sec. 2, flow paragraph and eq. 10); the per-pixel velocity
- * the detector hands on (Sec. 1).  Device-to-device copies on the context
+ * the detector hands on (Sec. 1).  A device-to-device copy on the context
  * stream; the buffers are the caller's.
  * Errors: RMDF_E_INVAL (NULL ctx), RMDF_E_STATE before the first push. */
 rmdf_status rmdf_velocity(rmdf_ctx *ctx, float *vxy_dev, int *idx_dev);

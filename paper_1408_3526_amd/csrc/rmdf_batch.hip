@@ -487,9 +487,8 @@ rmdf_status rmdf_batch_push(rmdf_batch* b, const float* const* frames) {
 
 rmdf_status rmdf_batch_output(rmdf_batch* b, int s, float* out, float* vxy, int* idx) {
   if (!b || s < 0 || s >= b->n) return bfail(b, RMDF_E_INVAL, "bad arguments");
-  rmdf_status st = RMDF_OK;
-  if (out) st = rmdf_output(b->ctx[s], out);
-  if (st == RMDF_OK && (vxy || idx)) st = rmdf_velocity(b->ctx[s], vxy, idx);
+  if (!out && !vxy && !idx) return RMDF_OK;
+  const rmdf_status st = rmdf_internal_read_out(b->ctx[s], out, vxy, idx);
   if (st != RMDF_OK) return bfail(b, st, rmdf_last_error(b->ctx[s]));
   return RMDF_OK;
 }

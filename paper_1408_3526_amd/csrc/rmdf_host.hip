@@ -308,6 +308,44 @@ unsigned long long* rmdf_internal_nonfinite(const rmdf_ctx* c) { return c->nonfi
 void rmdf_internal_shape(const rmdf_ctx* c, int* mx, int* my, int* mz, int* variant) {
   *mx = c->MX; *my = c->MY; *mz = c->MZ; *variant = c->variant;
 }
+// Memory of the context's device, which a kernel of its stream can write.
+static bool own_device_memory(const rmdf_ctx* c, const void* p) {
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == c->device;
+}
+
+// The latest frame's results into the caller's arrays (each may be NULL): one launch
+// where several arrays are wanted and all lie on the context's device, otherwise
+// a copy each.
+static rmdf_status read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
+  const size_t HW = (size_t)c->H * c->W;
+  const rmdf::CopyArgs a{{c->out, c->vxy, c->vidx}, {out, vxy, idx}, {out ? HW : 0, vxy ? 2 * HW : 0, idx ? HW : 0}};
+  int n = 0;
+  bool one = true;
+  for (int k = 0; k < 3; ++k) {
+    if (!a.dst[k]) continue;
+    ++n;
+    one = one && (reinterpret_cast<uintptr_t>(a.dst[k]) & 3) == 0 && own_device_memory(c, a.dst[k]);
+  }
+  hipError_t e = hipSuccess;
+  if (n > 1 && one) {
+    e = rmdf::launch_copy(a, c->stream);
+  } else {
+    for (int k = 0; k < 3 && e == hipSuccess; ++k)
+      if (a.dst[k]) e = hipMemcpyAsync(a.dst[k], a.src[k], a.words[k] * 4, hipMemcpyDeviceToDevice, c->stream);
+  }
+  return e == hipSuccess ? RMDF_OK : hip_fail(c, e, "result copy");
+}
+
+rmdf_status rmdf_internal_read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
+  if (c->t == 0) return fail(c, RMDF_E_STATE, "no frame pushed yet");
+  return read_out(c, out, vxy, idx);
+}
+
 void rmdf_internal_advance(rmdf_ctx* c) { c->t += 1; }
 void rmdf_internal_set_batch_owned(rmdf_ctx* c) { c->batch_owned = true; }
 
@@ -639,22 +677,14 @@ rmdf_status rmdf_push_frames(rmdf_ctx* c, int n, const float* const* frames, flo
 rmdf_status rmdf_velocity(rmdf_ctx* c, float* vxy, int* idx) {
   if (!c) return fail(nullptr, RMDF_E_INVAL, "ctx is NULL");
   if (c->t == 0) return fail(c, RMDF_E_STATE, "no frame pushed yet");
-  const size_t HW = (size_t)c->H * c->W;
-  hipError_t e;
-  if (vxy && (e = hipMemcpyAsync(vxy, c->vxy, HW * sizeof(float2), hipMemcpyDeviceToDevice, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "velocity copy");
-  if (idx && (e = hipMemcpyAsync(idx, c->vidx, HW * sizeof(int), hipMemcpyDeviceToDevice, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "index copy");
-  return RMDF_OK;
+  return read_out(c, nullptr, vxy, idx);
 }
 
 rmdf_status rmdf_output(rmdf_ctx* c, float* out) {
   if (!c) return fail(nullptr, RMDF_E_INVAL, "ctx is NULL");
   if (!out) return fail(c, RMDF_E_INVAL, "out is NULL");
   if (c->t == 0) return fail(c, RMDF_E_STATE, "no frame pushed yet");
-  hipError_t e = hipMemcpyAsync(out, c->out, (size_t)c->H * c->W * sizeof(float), hipMemcpyDeviceToDevice, c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "output copy");
-  return RMDF_OK;
+  return read_out(c, out, nullptr, nullptr);
 }
 
 rmdf_status rmdf_frames_pushed(const rmdf_ctx* c, long long* n) {

@@ -68,6 +68,14 @@ int pixel_block_columns(int mx, int my, int mz);
 // default rows per work tile for an H x W frame
 int auto_tile_rows(int H, int W, int block_columns);
 hipError_t launch_pixel(int mx, int my, int mz, const PixArgs& a, hipStream_t s);
+
+// Up to three arrays copied by one launch; destinations aligned to 4 bytes.
+struct CopyArgs {
+  const void* src[3];          // aligned to 16 bytes
+  void* dst[3];
+  size_t words[3];             // 32-bit words; 0: none
+};
+hipError_t launch_copy(const CopyArgs& a, hipStream_t s);
 // Whether the generic kernel's tiles compute their row spectra themselves
 // (PixArgs::frame) instead of reading the row kernel's.  They save a launch and
 // its latency and the row spectra's way through memory, and wait longer at

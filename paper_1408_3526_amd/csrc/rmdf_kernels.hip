@@ -99,7 +99,32 @@ __global__ void k_spectrum(const float2* __restrict__ st, int W, const int* __re
 }
 
 // ---------------------------------------------------------------------------
+// A frame's results copied out in one launch.  A copy of 16 to 33 KB is a launch
+// and little else (1.2 to 2 us each; 64x64 frames with three copies 18.2 us,
+// velocity and index in one launch 16.3), so the arrays share one; blockIdx.y
+// is the array.
+__global__ void __launch_bounds__(256) k_copy_out(CopyArgs a) {
+  const int k = blockIdx.y;
+  const size_t n = a.words[k], i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= n) return;
+  const unsigned* src = static_cast<const unsigned*>(a.src[k]) + i;
+  unsigned* dst = static_cast<unsigned*>(a.dst[k]) + i;
+  if (i + 4 <= n && (reinterpret_cast<uintptr_t>(a.dst[k]) & 15) == 0) {
+    *reinterpret_cast<v4u*>(dst) = *reinterpret_cast<const v4u*>(src);
+  } else {
+    for (int q = 0; q < 4 && i + q < n; ++q) dst[q] = src[q];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
+hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
+  const size_t n = std::max(std::max(a.words[0], a.words[1]), a.words[2]);
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_copy_out, dim3((unsigned)((n + 1023) / 1024), 3), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int MX, int MY, int MZ>
 static hipError_t launch_pixel_t(const PixArgs& a, hipStream_t s) {
   using SH = Shape<MX, MY, MZ>;
