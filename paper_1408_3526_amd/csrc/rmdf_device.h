@@ -170,10 +170,11 @@ static __device__ void row_chunk(const float* __restrict__ f, float2* __restrict
 // Against the form with workgroup barriers and loads in the candidate loop
 // (us per frame, output and velocity read): 9x9x5 640x512 941 -> 470 (4.25 TB/s of
 // cache-line traffic; the state and R alone would take 370 at the copy rate), 8x8x4
-// 640x512 397 -> 217, 16x16x8 319x241 with 33x33 candidates 1243 -> 537 (3.7 TB/s,
-// two wavefronts per SIMD; 391), the paper's 64x64 frames 24.4 -> 18.2.  Of these, row
-// spectra computed in the tiles give 16, 0, 10 and 1.8, and the state moved in
-// contiguous runs, non-temporal, 32, 22, 93 and 1.1.
+// 640x512 397 -> 217, 16x16x8 319x241 with 33x33 candidates 1243 -> 521 (3.8 TB/s,
+// two wavefronts per SIMD; 391), the paper's 64x64 frames 24.4 -> 16.2 (with the
+// kernel left out, launches and host calls take 12 to 13).  Of these, row spectra
+// computed in the tiles give 16, 0, 10 and 1.8, the state moved in contiguous runs,
+// non-temporal, 32, 22, 93 and 1.1, and the read-outs' shared launch 2 of the last.
 template <int MX, int MY, int MZ>
 struct Shape {
   static constexpr bool EVEN = (MX % 2 == 0);
@@ -465,8 +466,10 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
 
   // first row's state (and row spectra); later rows' are loaded one row ahead
   float2 Xn[NL][VL], in_n[CPL], in_o[CPL];
-  auto load_row = [&](int y) {
-    const auto src = buffer_of(a.st + ((size_t)y * a.W + xw) * (NCOL * MZ), st_bytes);
+  // (a row past the tile: an empty descriptor, and row spectra that are not used)
+  auto load_row = [&](int yy) {
+    const int y = CPL > 1 ? min(yy, y1 - 1) : yy;
+    const auto src = buffer_of(a.st + ((size_t)y * a.W + xw) * (NCOL * MZ), CPL == 1 || yy < y1 ? st_bytes : 0u);
     const float2* rn = a.rs + ((size_t)y * a.W + xw) * NP;
     const float2* rl = a.rs + ((size_t)max(y - MY, 0) * a.W + xw) * NP;
 #pragma unroll
@@ -525,16 +528,20 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     float2 X[CPL][MZ];
     float* rp = a.rsm + pix0 * nv;
     float rn[NB];
-    // smoothed R of the next NB candidates: (ROWS) NB / KX rounds from l_y = w on,
-    // places past the grid reading its last value; else from item w on, through a
-    // buffer descriptor of the anchors' values (reads past it give 0)
+    // smoothed R, through a buffer descriptor of the anchors' values (reads past it
+    // give 0, writes are dropped): every access is unconditional, so that a wait
+    // counts the accesses it can leave in flight.  A lane's first candidate, or (ROWS)
+    // first candidate u of KX:
     const auto rb = buffer_of(rp, 4u * (unsigned)(nv * (PPW == 1 ? 1 : min(PPW, a.W - xw))));
-    auto load_r = [&](int w) {
+    const unsigned r_step = 4u * (unsigned)(ROWS ? G * nvx : LPP);   // from one round's values to the next's
+    auto r_off = [&](int u) {
+      if (!ROWS) return qo + 4u * (unsigned)cl;
+      return iyC < G && ixC + u * LC < nvx ? qo + 4u * (unsigned)(iyC * nvx + ixC + u * LC) : BUFFER_NONE;
+    };
+    auto load_r = [&]() {                        // the first NB candidates'
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        if (ROWS) rn[i] = at(rp, qo + 4u * (unsigned)min((w + i / KX * G) * nvx + ixC + i % KX * LC, nv - 1));
-        else rn[i] = buffer_ld(rb, qo + 4u * (unsigned)(w + cl) + 4u * LPP * i);
-      }
+      for (int i = 0; i < NB; ++i)
+        rn[i] = ROWS ? buffer_ld(rb, r_off(i % KX) + (unsigned)(i / KX) * r_step) : buffer_ld(rb, r_off(0) + 4u * LPP * i);
     };
     wave_lds_sync();                             // the previous row's stage C reads are done
 #pragma unroll
@@ -595,13 +602,22 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
     // this row's smoothed R (first rounds of stage C), the delayed sample and
     // the next row's state are in flight during the flow stages; stage C waits
     // for the first group only (vector memory completes in order)
-    load_r(ROWS ? iyC : 0);
+    load_r();
     float idel = 0.f;
     {
       const int xs = x - a.dx, ys = y - a.dy;
-      if (ring_delayed != nullptr && xs >= 0 && ys >= 0) idel = ring_delayed[(size_t)ys * a.W + xs];
+      const bool ok = ring_delayed != nullptr && xs >= 0 && ys >= 0;
+      if (CPL > 1) {
+        const float v = *(ok ? ring_delayed + (size_t)ys * a.W + xs : a.gx);
+        idel = ok ? v : 0.f;
+      } else if (ok) {
+        idel = ring_delayed[(size_t)ys * a.W + xs];
+      }
     }
-    if (y + 1 < y1) load_row(y + 1);
+    // (unconditional where the wait for R that follows can then leave the next row's
+    // state in flight: 33x33 candidates 534 -> 521 us; the small windows lose 1% by
+    // the empty accesses of a tile's last row)
+    if (CPL > 1 || y + 1 < y1) load_row(y + 1);
 
     // ---- high-pass (drop kx = ky = 0 for every kz) and Hann along kz.
     // Hann along an axis is Y(k) = (2X(k) - X(k-1) - X(k+1)) / 4; the 1/4 per
@@ -760,50 +776,53 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
         for (int kx = 0; kx < NXH; ++kx) r += t[kx].x * w_x[kx].x - t[kx].y * w_x[kx].y;
         return (1.f - a.alpha) * r + a.alpha * r_prev;
       };
+      // A lane's candidates come in rising order, so only a larger value takes
+      // over, and the round it came in is all that is kept (a grid without a value
+      // above -infinity: below).
+      int br = -1;
+      auto keep = [&](float sm, int rnd, bool ok, unsigned off) {
+        buffer_st(rb, sm, PPW == 1 || ok ? off : BUFFER_NONE);
+        const bool take = (sm > bv) & ok;
+        bv = take ? sm : bv;
+        br = take ? rnd : br;
+      };
       if constexpr (ROWS) {
-        float rc[NB];
+        unsigned vo[KX];
 #pragma unroll
-        for (int u = 0; u < KX; ++u) ld_col<NXH>(s_taux + min(ixC + u * LC, nvx - 1) * NXT, tx[u]);
-        for (int iy0 = 0; iy0 < nvy; iy0 += NB / KX * G) {
+        for (int u = 0; u < KX; ++u) {
+          vo[u] = r_off(u);
+          ld_col<NXH>(s_taux + min(ixC + u * LC, nvx - 1) * NXT, tx[u]);
+        }
+        int o_t = min(iyC, nvy - 1) * NXT, rnd = 0;
+        // (leaving inside the group, not skipping a round of it: on the way back every
+        // access has been issued)
+        for (int iy0 = 0; iy0 < nvy;) {
 #pragma unroll
-          for (int i = 0; i < NB; ++i) rc[i] = rn[i];
-          if (iy0 + NB / KX * G < nvy) load_r(iy0 + NB / KX * G + iyC);
+          for (int v = 0; v < NB / KX; ++v, iy0 += G) {
+            if (v > 0 && iy0 >= nvy) break;
+            ld_col<NXH>(s_t + o_t, t);
+            o_t = min(o_t + G * NXT, (nvy - 1) * NXT);
 #pragma unroll
-          for (int v = 0; v < NB / KX; ++v) {
-            const int iy = iy0 + v * G + iyC;
-            if (iyC < G && iy < nvy) {           // lanes past the last whole group idle
-              ld_col<NXH>(s_t + iy * NXT, t);
-#pragma unroll
-              for (int u = 0; u < KX; ++u)
-                if (ixC + u * LC < nvx) {
-                  const int w = iy * nvx + ixC + u * LC;
-                  const float sm = smooth(tx[u], rc[v * KX + u]);
-                  if (px_ok) at(rp, qo + 4u * (unsigned)w) = sm;
-                  amax_merge(bv, bi, sm, w);
-                }
+            for (int u = 0; u < KX; ++u, ++rnd) {
+              keep(smooth(tx[u], rn[v * KX + u]), rnd, vo[u] < 4u * (unsigned)nv, vo[u]);
+              rn[v * KX + u] = buffer_ld(rb, vo[u] + NB / KX * r_step);
+              vo[u] += r_step;
             }
             __builtin_amdgcn_sched_barrier(0);   // one round's LDS reads in flight at a time
           }
         }
+        const int rr = br / KX;
+        bi = br < 0 ? 0x7fffffff : (rr * G + iyC) * nvx + ixC + (br - rr * KX) * LC;
       } else {
-        // A lane's candidates come in rising order, so only a larger value takes
-        // over, and the round it came in is all that is kept (a grid without a value
-        // above -infinity: below).  Whole groups have no lane past the grid.
-        int br = -1;
-        unsigned vo = qo + 4u * (unsigned)cl;
+        unsigned vo = r_off(0);
         const lds_u32* it = s_itC + cl;
         unsigned itC = it[0];
-        auto round = [&](int i, int rnd, bool ok, bool whole) {
+        auto round = [&](int i, int rnd, bool ok, bool whole) {   // (whole groups have no lane past the grid)
           const unsigned o = itC;
           itC = it[(i + 1) * LPP];
           ld_col<NXH>(lds_at(s_t, o & 0xffffu), t);
           ld_col<NXH>(lds_at(s_taux, o >> 16), tx[0]);
-          const float sm = smooth(tx[0], rn[i]);
-          // (one anchor: the descriptor ends with its values)
-          buffer_st(rb, sm, (PPW == 1 || whole || ok ? vo : BUFFER_NONE) + 4u * LPP * i);
-          const bool take = (sm > bv) & (whole | ok);
-          bv = take ? sm : bv;
-          br = take ? rnd : br;
+          keep(smooth(tx[0], rn[i]), rnd, whole | ok, vo + 4u * LPP * i);
           __builtin_amdgcn_sched_barrier(0);
         };
         int w0 = 0, rnd = 0;
@@ -823,7 +842,7 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
       }
     }
     group_amax<LPP>(bv, bi);
-    if (!ROWS && __any(bv == -INFINITY)) {       // overflowed: the first candidate of -infinity, if one is
+    if (__any(bv == -INFINITY)) {       // overflowed: the first candidate of -infinity, if one is
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
