@@ -23,14 +23,14 @@
 //
 // What bounds it (640x512, 17x17 candidates): one observer frame its HBM bytes
 // (1.16 ms a frame, 5.2 TB/s); the forms that move half of them (frame pairs,
-// the ring) the VALU, 1 050 instructions an anchor and frame, 85% busy in the
-// ring.  So those forms run three wavefronts per SIMD (at most 168 registers,
-// 50.7 KB of LDS per workgroup) and leave latency to the other wavefronts, and
-// the modes that stream a whole observer state run two with the next row's state
-// loaded one row ahead (three without: 1.20 against 1.18 ms).  Against two
-// wavefronts with the prefetch throughout, four passes along kx and one candidate
-// per T read in stage C: ring 1.10 -> 0.82 ms, pairs 1.06 -> 0.75 ms a frame
-// (the pairs' last 0.14 ms from loads that need no full wait and no spills),
+// the ring) the VALU, 1 100 instructions an anchor and frame, 86% busy in the
+// ring and 92% in the pairs.  So those forms run three wavefronts per SIMD (at
+// most 168 registers, 50.7 KB of LDS per workgroup) and leave latency to the other
+// wavefronts, and the modes that stream a whole observer state run two with the
+// next row's state loaded one row ahead (three without: 1.20 against 1.18 ms).
+// Against two wavefronts with the prefetch throughout, four passes along kx and
+// one candidate per T read in stage C: ring 1.10 -> 0.82 ms, pairs 1.06 -> 0.75 ms
+// a frame (the pairs' last 0.14 ms from loads that need no full wait and no spills),
 // refined 317x243 0.336 -> 0.297 ms, single frames 1.23 -> 1.17 ms.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -173,8 +173,8 @@ static __device__ __forceinline__ int order_key(int b) { return b ^ ((b >> 31) &
 
 // The group's maximum v (never NaN: running maxima that began at -infinity)
 // and the lowest i that holds it: the maximum first, as an integer key (one DPP
-// instruction per level; a float maximum would quiet its operands first), then the index from the one lane that equals it, or from the lowest
-// where several do.
+// instruction per level; a float maximum would quiet its operands first), then the
+// index from the one lane that equals it, or the lowest where several do.
 template <int G>
 static __device__ __forceinline__ void group_amax(float& v, int& i) {
   const float m = __int_as_float(order_key(group_ext<G, true>(order_key(__float_as_int(v)))));

@@ -63,3 +63,29 @@ def test_batch_outputs_are_ordered_with_the_callers_stream():
     for f in fs:
         f.close()
     b.close()
+
+
+def test_velocity_under_capture():
+    """A captured read-out, replayed between frames pushed outside the graph,
+    gives each frame's velocity and index."""
+    H, W, T = 21, 30, 6
+    g = scenes.grid(-2, 2, 0.5)
+    fr = torch.from_numpy(scenes.flow_scene(4, H=H, W=W, T=T, n_targets=1).frames).cuda()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    f = binding.Filter(H, W, 8, 8, 4, g, g, stream=s.cuda_stream)
+    v, i = torch.empty(H, W, 2, device="cuda"), torch.empty(H, W, dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        f.push_frame(fr[0])
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            f.velocity(v, i)
+        for t in range(1, T):
+            f.push_frame(fr[t])
+            graph.replay()
+            a, b = (x.clone() for x in (v, i))
+            c, d = f.velocity()
+            assert torch.equal(a, c) and torch.equal(b, d), t
+    torch.cuda.synchronize()
+    f.close()
