@@ -407,9 +407,9 @@ static __device__ __forceinline__ void pixel_tile(const PixArgs& a, const float*
   // an anchor, 61 when contiguous; 505 -> 475 us).  So the state moves between memory
   // and LDS in contiguous runs, one piece of VL values per lane, and between LDS and
   // registers by column.  Non-temporal: a stream of less than 256 MB that runs
-  alone could stay in the chip's last cache (8x8x4 320x256 with detection 63.5 us
-  cached, 70.2 this way), but streams that take turns could not (75.7 and 70.5), nor
-  larger ones (8x8x4 640x512 alone 224 and 206).
+  // alone could stay in the chip's last cache (8x8x4 320x256 with detection 63.5 us
+  // cached, 70.2 this way), but streams that take turns could not (75.7 and 70.5), nor
+  // larger ones (8x8x4 640x512 alone 224 and 206).
   constexpr int VL = (MZ % 2 == 0) ? 2 : 1;      // float2 per piece
   constexpr int CS = (MZ % 2 == 0) ? MZP : MZ;   // column stride in LDS (padded: distinct banks)
   constexpr int NPC = NCOL * MZ / VL, NL = (NPC + LPP - 1) / LPP;   // pieces per anchor and lane
