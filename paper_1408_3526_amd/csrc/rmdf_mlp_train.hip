@@ -75,6 +75,10 @@ __global__ void __launch_bounds__(256) k_train_rows(const unsigned short* __rest
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * TR;
+  // samples of this tile (a multiple of 8).  The sums over samples stop here: the
+  // rows past n hold row n - 1 again with a zero gradient, and zero times an
+  // overflowed activation is not zero.
+  const int rows = min(TR, n - m0);
   float* P = part + (size_t)blockIdx.x * P_N;
 
   // the tile's features straight into LDS: 1 KB per load, rows past n re-read
@@ -219,8 +223,9 @@ __global__ void __launch_bounds__(256) k_train_rows(const unsigned short* __rest
   if (tid < 3 * N2) {
     const int q = tid / N2, j = tid % N2;
     float s = 0.f;
-#pragma unroll 8
-    for (int r = 0; r < TR; ++r) s += sD[q][r] * h2(r, j);
+    for (int r0 = 0; r0 < rows; r0 += 8)
+#pragma unroll
+      for (int r = r0; r < r0 + 8; ++r) s += sD[q][r] * h2(r, j);
     P[tid] = s;
   }
   __syncthreads();
@@ -228,8 +233,9 @@ __global__ void __launch_bounds__(256) k_train_rows(const unsigned short* __rest
   // ---- dH1 = (dH2 W2) masked by H1 > 0; column sums of dH2 and dH1
   if (tid < N2) {
     float s = 0.f;
-#pragma unroll 8
-    for (int r = 0; r < TR; ++r) s += bf16_float(sG[r * N2 + (((tid >> 3) ^ (r & 7)) * 8) + (tid & 7)]);
+    for (int r0 = 0; r0 < rows; r0 += 8)
+#pragma unroll
+      for (int r = r0; r < r0 + 8; ++r) s += bf16_float(sG[r * N2 + (((tid >> 3) ^ (r & 7)) * 8) + (tid & 7)]);
     P[P_DB2 + tid] = s;
   }
   f32x16 ag;
@@ -247,7 +253,7 @@ __global__ void __launch_bounds__(256) k_train_rows(const unsigned short* __rest
     const int at = row * N1 + (((col >> 3) ^ (row & 15)) * 8) + (col & 7);
     const unsigned short v = bf16_bits((bf16_float(sH1[at]) > 0.f) ? ag[i] : 0.f);
     sX[at] = v;
-    cs += bf16_float(v);
+    cs += row < rows ? bf16_float(v) : 0.f;
   }
   cs += __shfl_xor(cs, 32, 64);
   if (h == 0) P[P_DB1 + col] = cs;
