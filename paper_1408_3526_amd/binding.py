@@ -609,13 +609,30 @@ def mlp_grads_work(n: int) -> int:
     return b.value
 
 
+_MLP_SHAPES = {"W1": (128, 1152), "b1": (128,), "W2": (64, 128), "b2": (64,), "W3": (3, 64), "b3": (3,)}
+_MLP_NUMEL = {k: int(np.prod(v)) for k, v in _MLP_SHAPES.items()}
+
+
 def mlp_grads(X, labels, W1, b1, W2, b2, W3, b3, wv, half_step, grads, loss, work):
-    """rmdf_mlp_grads: loss and gradients of one batch; grads: dict of FP32
-    tensors W1, b1, W2, b2, W3, b3; work: uint8 scratch."""
-    g = [grads[k].data_ptr() for k in ("W1", "b1", "W2", "b2", "W3", "b3")]
-    _check(lib().rmdf_mlp_grads(X.data_ptr(), labels.data_ptr(), X.shape[0], W1.data_ptr(), b1.data_ptr(),
-                                W2.data_ptr(), b2.data_ptr(), W3.data_ptr(), b3.data_ptr(), float(wv),
-                                float(half_step), *g, loss.data_ptr(), work.data_ptr(), work.numel(),
+    """rmdf_mlp_grads: loss and gradients of one batch.  X: [n, 1152] bfloat16;
+    labels: float32, the first n pairs are used; W1, W2 bfloat16, the other
+    parameters float32; grads: dict of float32 tensors W1, b1, W2, b2, W3, b3;
+    loss: one float32; work: uint8 scratch of mlp_grads_work(n) bytes.  All
+    contiguous and on the HIP device: the kernels take their shapes for granted."""
+    import torch
+    f32, bf16 = torch.float32, torch.bfloat16
+    if X.dim() != 2 or X.shape[1] != 1152:
+        raise ValueError("X must have shape [n, 1152], has %s" % (tuple(X.shape),))
+    n = X.shape[0]
+    if labels.numel() < 2 * n:
+        raise ValueError("labels must have at least %d elements, has %d" % (2 * n, labels.numel()))
+    num = _MLP_NUMEL
+    p = [_dev_ptr(t, d, num[k], k) for t, d, k in ((W1, bf16, "W1"), (b1, f32, "b1"), (W2, bf16, "W2"), (b2, f32, "b2"),
+                                                   (W3, f32, "W3"), (b3, f32, "b3"))]
+    g = [_dev_ptr(grads[k], f32, num[k], "gradient of " + k) for k in num]
+    _check(lib().rmdf_mlp_grads(_dev_ptr(X, bf16, None, "X"), _dev_ptr(labels, f32, None, "labels"), n, *p, float(wv),
+                                float(half_step), *g, _dev_ptr(loss, f32, 1, "loss"),
+                                _dev_ptr(work, torch.uint8, None, "work"), work.numel(),
                                 ctypes.c_void_p(_stream_handle())))
 
 
