@@ -142,6 +142,8 @@ class Trainer:
     def grads(self, X, lab):
         """Loss and gradients of one batch (into self.g); returns the loss tensor."""
         b, u, p = self.b, self.buf, self.p
+        if X.data_ptr() % 16:        # a view at an odd place: the kernels load 16 bytes at a time
+            X = X.clone()
         work = u["work"]
         if X.shape[0] != self.batch:
             work = self.torch.empty(b.mlp_grads_work(X.shape[0]), dtype=self.torch.uint8, device="cuda")

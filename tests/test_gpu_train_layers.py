@@ -82,3 +82,21 @@ def test_batches_of_another_shape_are_refused():
     assert all(torch.equal(tr.g[k], want[k]) for k in want)
     tr.grads(X, torch.zeros(2 * n, 2, device="cuda"))
     assert all(torch.equal(tr.g[k], want[k]) for k in want)
+
+
+@pytest.mark.parametrize("off", [1, 4, 7])
+def test_features_at_any_address(off):
+    """Contiguous features that begin at an address no multiple of 16 bytes."""
+    from mlp_cases import random_params
+    rng = np.random.default_rng(off)
+    n = 40
+    tr = _trainer_with(random_params(rng), n)
+    X, lab = _bf(rng.normal(size=(n, mlp.N_IN))), torch.from_numpy(rng.normal(size=(n, 2)).astype(np.float32)).cuda()
+    loss = tr.grads(X, lab).clone()
+    want = {k: v.clone() for k, v in tr.g.items()}
+    flat = torch.empty(off + n * mlp.N_IN, dtype=torch.bfloat16, device="cuda")
+    view = flat[off:].view(n, mlp.N_IN)
+    view.copy_(X)
+    assert view.data_ptr() % 16 == 2 * off
+    assert torch.equal(tr.grads(view, lab), loss)
+    assert all(torch.equal(tr.g[k], want[k]) for k in want)
