@@ -308,19 +308,23 @@ unsigned long long* rmdf_internal_nonfinite(const rmdf_ctx* c) { return c->nonfi
 void rmdf_internal_shape(const rmdf_ctx* c, int* mx, int* my, int* mz, int* variant) {
   *mx = c->MX; *my = c->MY; *mz = c->MZ; *variant = c->variant;
 }
-// Memory of the context's device, which a kernel of its stream can write.
-static bool own_device_memory(const rmdf_ctx* c, const void* p) {
+// Memory of the context's device, which a kernel of its stream can write, all
+// `bytes` of it within one allocation.
+static bool own_device_memory(const rmdf_ctx* c, void* p, size_t bytes) {
   hipPointerAttribute_t at;
-  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipMemGetAddressRange(&base, &size, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return at.type == hipMemoryTypeDevice && at.device == c->device;
+  const size_t first = static_cast<size_t>(static_cast<char*>(p) - static_cast<char*>(base));
+  return at.type == hipMemoryTypeDevice && at.device == c->device && first <= size && bytes <= size - first;
 }
 
 // The latest frame's results into the caller's arrays (each may be NULL): one launch
 // where several arrays are wanted and all lie on the context's device, otherwise
-// a copy each.
+// a copy each (which HIP refuses where the array's allocation is too small).
 static rmdf_status read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
   const size_t HW = (size_t)c->H * c->W;
   const rmdf::CopyArgs a{{c->out, c->vxy, c->vidx}, {out, vxy, idx}, {out ? HW : 0, vxy ? 2 * HW : 0, idx ? HW : 0}};
@@ -329,7 +333,7 @@ static rmdf_status read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
   for (int k = 0; k < 3; ++k) {
     if (!a.dst[k]) continue;
     ++n;
-    one = one && (reinterpret_cast<uintptr_t>(a.dst[k]) & 3) == 0 && own_device_memory(c, a.dst[k]);
+    one = one && (reinterpret_cast<uintptr_t>(a.dst[k]) & 3) == 0 && own_device_memory(c, a.dst[k], a.words[k] * 4);
   }
   hipError_t e = hipSuccess;
   if (n > 1 && one) {
