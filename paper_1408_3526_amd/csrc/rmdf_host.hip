@@ -342,7 +342,9 @@ static rmdf_status read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
     for (int k = 0; k < 3 && e == hipSuccess; ++k)
       if (a.dst[k]) e = hipMemcpyAsync(a.dst[k], a.src[k], a.words[k] * 4, hipMemcpyDeviceToDevice, c->stream);
   }
-  return e == hipSuccess ? RMDF_OK : hip_fail(c, e, "result copy");
+  if (e == hipSuccess) return RMDF_OK;
+  (void)hipGetLastError();   // reported here; the next launch's check shall not find it again
+  return hip_fail(c, e, "result copy");
 }
 
 rmdf_status rmdf_internal_read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {

@@ -121,8 +121,11 @@ __global__ void __launch_bounds__(256) k_copy_out(CopyArgs a) {
 hipError_t launch_copy(const CopyArgs& a, hipStream_t s) {
   const size_t n = std::max(std::max(a.words[0], a.words[1]), a.words[2]);
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_out, dim3((unsigned)((n + 1023) / 1024), 3), dim3(256), 0, s, a);
-  return hipGetLastError();
+  // the launch's own status: an error that an earlier call of the program's has left
+  // behind is none of this copy's
+  void* args[] = {const_cast<CopyArgs*>(&a)};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k_copy_out), dim3((unsigned)((n + 1023) / 1024), 3), dim3(256),
+                         args, 0, s);
 }
 
 template <int MX, int MY, int MZ>

@@ -55,7 +55,8 @@ def test_a_short_velocity_array_is_refused(short, inside):
     assert L.rmdf_velocity(f.ctx, *one) == binding.RMDF_E_DEVICE
     assert L.rmdf_velocity(f.ctx, v.p + inside, i.p + inside) == binding.RMDF_E_DEVICE
     assert (bad.host() == 0x55).all()
-    v.hip.hipGetLastError()
+    f.velocity()                                 # the context goes on
+    f.push_frame(torch.zeros(H, W, device="cuda"))
     v.free()
     i.free()
     f.close()
@@ -69,10 +70,27 @@ def test_a_short_batch_output_is_refused(short):
     a = [DeviceArray(k * N - (64 if q == short else 0)) for q, k in enumerate((4, 8, 4))]
     assert binding.lib().rmdf_batch_output(b.b, 0, *(x.p for x in a)) == binding.RMDF_E_DEVICE
     assert (a[short].host() == 0x55).all()
-    a[0].hip.hipGetLastError()
+    b.output(0)
     for x in a:
         x.free()
     b.close()
+
+
+def test_an_error_left_by_another_call_is_not_reported():
+    """HIP keeps the status of a program's last failed call until it is asked for."""
+    g = scenes.grid(-2, 2, 0.5)
+    f = binding.Filter(H, W, 8, 8, 4, g, g)
+    f.push_frame(torch.randn(H, W, device="cuda"))
+    want = f.velocity()
+    v, i = torch.empty(H, W, 2, device="cuda"), torch.empty(H, W, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipMemcpy(None, None, ctypes.c_size_t(16), 3) != 0      # refused for its NULL arguments
+    st = binding.lib().rmdf_velocity(f.ctx, v.data_ptr(), i.data_ptr())
+    hip.hipGetLastError()
+    assert st == binding.RMDF_OK
+    assert torch.equal(v, want[0]) and torch.equal(i, want[1])
+    f.close()
 
 
 @pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
