@@ -147,7 +147,10 @@ void launch_cfar(const float* x, int H, int W, int G, int R, float k, unsigned c
 // of the small and 2 of the large fit a CU (LDS), the large ones ending in whole
 // rounds.  (us, 4 and 16 rows: 320x256 R = 6 4.1 and 8.1; 640x512 R = 6 7.2 and 8.5,
 // R = 16 17.4 and 13.6; 1280x1024 R = 1 13.7 and 14.6, R = 3 21.2 and 18.4.)
+// (A launch is limited to 65536 rows of workgroups: images of more rows of small
+// tiles than that take the large ones.)
 bool short_tiles(int H, int W, int R) {
+  if ((H + 3ll) / 4 > 65535) return false;
   const long long xb = (W + CF_TW - 1) / CF_TW, n4 = xb * ((H + 3) / 4), n16 = xb * ((H + 15) / 16);
   return std::max(n4, 768ll) * (4 + 2 * R) < 768 * ((n16 + 511) / 512) * (16 + 2 * R);
 }
