@@ -100,3 +100,62 @@ def test_features_at_any_address(off):
     assert view.data_ptr() % 16 == 2 * off
     assert torch.equal(tr.grads(view, lab), loss)
     assert all(torch.equal(tr.g[k], want[k]) for k in want)
+
+
+def layer_by_layer(tr, X, lab):
+    """Loss, gradients and the BF16 intermediates H1, dH2, dH1 of one batch, a call
+    per layer; the head adds its sums to what its outputs hold."""
+    b, n = tr.b, X.shape[0]
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    g = {k: torch.zeros_like(v) for k, v in tr.g.items()}
+    loss = torch.zeros(1, device="cuda")
+    H1, H2, dH2, dH1 = (torch.empty(n, m, **bf) for m in (mlp.N_H1, mlp.N_H2, mlp.N_H2, mlp.N_H1))
+
+    def t(x):
+        out = torch.empty(x.shape[1], x.shape[0], **bf)
+        b.mlp_transpose(x, out)
+        return out
+    tr.forward(X, H1, H2)
+    b.mlp_head(H2, tr.p["W3"], tr.p["b3"], lab, tr.wv, tr.half_step, dH2, g["W3"], g["b3"], loss)
+    b.mlp_gemm_nt(t(dH2), t(H1), out_f32=g["W2"])                  # dW2 = dH2^T H1
+    b.mlp_colsum(dH2, g["b2"])
+    b.mlp_gemm_nt(dH2, t(tr.bf["W2"]), epi=2, aux=H1, out_bf16=dH1)   # dH1 = dH2 W2 where H1 > 0
+    b.mlp_gemm_nt(t(dH1), t(X), out_f32=g["W1"])                   # dW1 = dH1^T X
+    b.mlp_colsum(dH1, g["b1"])
+    return loss, g, (H1, dH2, dH1)
+
+
+@pytest.mark.parametrize("n", [8, 24, 64, 72, 200, 1096])
+def test_the_layers_one_by_one(n):
+    """The layer-by-layer calls inside the intervals derived for FP32 accumulation
+    in any order, and their BF16 intermediates the bits that the three launches
+    leave in their scratch (H1, dH2, dH1, each section on 256 bytes)."""
+    from mlp_cases import random_params
+    rng = np.random.default_rng(300 + n)
+    X = mlp.bf16_round(rng.normal(size=(n, mlp.N_IN)))
+    params = random_params(rng)
+    O = mlp.forward(X, params)[-1]
+    lab = np.float32(O[:, :2] + rng.choice([-1, 1], (n, 2)) * rng.choice([0.1, 0.5], (n, 1)))
+    tr = _trainer_with(params, n)
+    Xd, labd = _bf(X), torch.from_numpy(lab).cuda()
+    loss, g, layers = layer_by_layer(tr, Xd, labd)
+    (lm, lr), want = mlp.grads_iv(X, lab, params, wv=tr.wv, half_step=tr.half_step)
+    assert mlp.within(float(loss.item()), lm, lr)
+    for k, (mid, rad) in want.items():
+        assert mlp.within(g[k].cpu().numpy().astype(np.float64), mid, rad).all(), k
+    tr.grads(Xd, labd)
+    at = 0
+    for name, t in zip(("H1", "dH2", "dH1"), layers):
+        nb = t.numel() * 2
+        got = tr.buf["work"][at:at + nb].view(torch.int16)
+        assert torch.equal(got, t.reshape(-1).view(torch.int16)), name
+        at += (nb + 255) // 256 * 256
+    if n > 64:
+        return
+    # the head's sums are added to what is there (one wavefront: one addition)
+    H2, d = (torch.empty(n, mlp.N_H2, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    tr.forward(Xd, layers[0], H2)
+    more = [torch.full_like(x, 3.0) for x in (g["W3"], g["b3"], loss)]
+    tr.b.mlp_head(H2, tr.p["W3"], tr.p["b3"], labd, tr.wv, tr.half_step, d, *more)
+    for x, y in zip(more, (g["W3"], g["b3"], loss)):
+        assert torch.equal(x, 3.0 + y)
