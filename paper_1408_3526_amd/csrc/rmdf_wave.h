@@ -45,6 +45,17 @@ static __device__ __forceinline__ lds_v2* lds_at(lds_v2* base, unsigned bytes) {
   return (lds_v2*)((RMDF_LDS char*)base + bytes);
 }
 
+// A pointer and an int that all lanes share although the compiler cannot see it
+// (arguments of a function that is called, not inlined): held in scalar registers.
+template <class T>
+static __device__ __forceinline__ T* uniform(T* p) {
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+  return reinterpret_cast<T*>((unsigned long long)hi << 32 | lo);
+}
+static __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Buffer descriptor of `bytes` bytes at p (the same in all lanes).  Reads past it
 // give 0 and writes past it are dropped, so lanes past the end of a run need
 // neither a mask nor a clamped index; BUFFER_NONE (with a small constant added)
