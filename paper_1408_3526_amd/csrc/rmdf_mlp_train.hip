@@ -393,10 +393,10 @@ struct Work {
 };
 static Work work_of(int n) {
   Work k;
-  k.tiles = (n + TR - 1) / TR;
-  const int blocks = (n + KB - 1) / KB;          // steps of KB samples
-  k.rows = ((blocks + WG_MAX_CHUNKS - 1) / WG_MAX_CHUNKS) * KB;
-  k.chunks = (n + k.rows - 1) / k.rows;
+  k.tiles = (n - 1) / TR + 1;                    // (n >= 8; n + TR may not be an int)
+  const int blocks = (n - 1) / KB + 1;           // steps of KB samples
+  k.rows = ((blocks - 1) / WG_MAX_CHUNKS + 1) * KB;
+  k.chunks = (n - 1) / k.rows + 1;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
