@@ -627,12 +627,19 @@ def mlp_grads(X, labels, W1, b1, W2, b2, W3, b3, wv, half_step, grads, loss, wor
     if labels.numel() < 2 * n:
         raise ValueError("labels must have at least %d elements, has %d" % (2 * n, labels.numel()))
     num = _MLP_NUMEL
-    p = [_dev_ptr(t, d, num[k], k) for t, d, k in ((W1, bf16, "W1"), (b1, f32, "b1"), (W2, bf16, "W2"), (b2, f32, "b2"),
-                                                   (W3, f32, "W3"), (b3, f32, "b3"))]
-    g = [_dev_ptr(grads[k], f32, num[k], "gradient of " + k) for k in num]
-    _check(lib().rmdf_mlp_grads(_dev_ptr(X, bf16, None, "X"), _dev_ptr(labels, f32, None, "labels"), n, *p, float(wv),
-                                float(half_step), *g, _dev_ptr(loss, f32, 1, "loss"),
-                                _dev_ptr(work, torch.uint8, None, "work"), work.numel(),
+    ptr = []
+    for name, t, dtype, numel in (
+            ("X", X, bf16, n * 1152), ("labels", labels, f32, labels.numel()),
+            ("W1", W1, bf16, num["W1"]), ("b1", b1, f32, num["b1"]), ("W2", W2, bf16, num["W2"]), ("b2", b2, f32, num["b2"]),
+            ("W3", W3, f32, num["W3"]), ("b3", b3, f32, num["b3"]),
+            ("gradient of W1", grads["W1"], f32, num["W1"]), ("gradient of b1", grads["b1"], f32, num["b1"]),
+            ("gradient of W2", grads["W2"], f32, num["W2"]), ("gradient of b2", grads["b2"], f32, num["b2"]),
+            ("gradient of W3", grads["W3"], f32, num["W3"]), ("gradient of b3", grads["b3"], f32, num["b3"]),
+            ("loss", loss, f32, 1), ("work", work, torch.uint8, work.numel())):
+        if not (t.is_cuda and t.dtype is dtype and t.numel() == numel and t.is_contiguous()):
+            _dev_ptr(t, dtype, numel, name)              # raises, naming what is wrong
+        ptr.append(t.data_ptr())
+    _check(lib().rmdf_mlp_grads(ptr[0], ptr[1], n, *ptr[2:8], float(wv), float(half_step), *ptr[8:], work.numel(),
                                 ctypes.c_void_p(_stream_handle())))
 
 
