@@ -324,15 +324,19 @@ static bool own_device_memory(const rmdf_ctx* c, void* p, size_t bytes) {
 
 // The latest frame's results into the caller's arrays (each may be NULL): one launch
 // where several arrays are wanted and all lie on the context's device, otherwise
-// a copy each (which HIP refuses where the array's allocation is too small).
+// a copy each (which HIP refuses where the array's allocation is too small; of
+// arrays that overlap the later one's values stand, so they go in turn too).
 static rmdf_status read_out(rmdf_ctx* c, float* out, float* vxy, int* idx) {
   const size_t HW = (size_t)c->H * c->W;
   const rmdf::CopyArgs a{{c->out, c->vxy, c->vidx}, {out, vxy, idx}, {out ? HW : 0, vxy ? 2 * HW : 0, idx ? HW : 0}};
   int n = 0;
   bool one = true;
+  auto begin = [&](int k) { return reinterpret_cast<uintptr_t>(a.dst[k]); };
   for (int k = 0; k < 3; ++k) {
     if (!a.dst[k]) continue;
     ++n;
+    for (int q = 0; q < k; ++q)
+      if (a.dst[q] && begin(q) < begin(k) + a.words[k] * 4 && begin(k) < begin(q) + a.words[q] * 4) one = false;
     one = one && (reinterpret_cast<uintptr_t>(a.dst[k]) & 3) == 0 && own_device_memory(c, a.dst[k], a.words[k] * 4);
   }
   hipError_t e = hipSuccess;

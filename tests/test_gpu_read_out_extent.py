@@ -76,6 +76,24 @@ def test_a_short_batch_output_is_refused(short):
     b.close()
 
 
+@pytest.mark.parametrize("shift", [0, 1, N - 1, 2 * N - 1, -1, 1 - N])
+def test_overlapping_arrays_hold_the_index(shift):
+    """An index array that shares memory with the velocity array: the index is
+    written after the velocities."""
+    g = scenes.grid(-2, 2, 0.5)
+    f = binding.Filter(H, W, 8, 8, 4, g, g)
+    for _ in range(5):
+        f.push_frame(torch.randn(H, W, device="cuda") * 10)
+    v, i = (x.reshape(-1) for x in f.velocity())
+    buf = torch.zeros(4 * N, device="cuda")
+    want = buf.clone()
+    want[N:3 * N] = v
+    want[N + shift:2 * N + shift] = i.view(torch.float32)
+    f.velocity(buf[N:3 * N], buf.view(torch.int32)[N + shift:2 * N + shift])
+    assert torch.equal(buf.view(torch.int32), want.view(torch.int32))
+    f.close()
+
+
 def test_an_error_left_by_another_call_is_not_reported():
     """HIP keeps the status of a program's last failed call until it is asked for."""
     g = scenes.grid(-2, 2, 0.5)
