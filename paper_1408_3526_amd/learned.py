@@ -131,7 +131,7 @@ class Trainer:
         self.lr, self.wv, self.half_step, self.batch = lr, wv, half_step, batch
         self.step_n = 0
         # scratch of a batch's forward and backward pass, and its loss
-        self.buf = {"work": torch.empty(b.mlp_grads_work(-(-batch // 8) * 8), dtype=torch.uint8, device=dev),
+        self.buf = {"work": torch.empty(b.mlp_grads_work(max(8, -(-batch // 8) * 8)), dtype=torch.uint8, device=dev),
                     "loss": torch.zeros(1, device=dev)}
 
     def forward(self, X, H1, H2):

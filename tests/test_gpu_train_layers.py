@@ -159,3 +159,10 @@ def test_the_layers_one_by_one(n):
     tr.b.mlp_head(H2, tr.p["W3"], tr.p["b3"], labd, tr.wv, tr.half_step, d, *more)
     for x, y in zip(more, (g["W3"], g["b3"], loss)):
         assert torch.equal(x, 3.0 + y)
+
+
+def test_a_trainer_without_batches():
+    """A Trainer made for its weights alone."""
+    from paper_1408_3526_amd import learned
+    tr = learned.Trainer(seed=3, batch=0)
+    assert tr.blob().size == mlp.N_H1 * mlp.N_IN + mlp.N_H1 + mlp.N_H2 * mlp.N_H1 + mlp.N_H2 + 3 * mlp.N_H2 + 3
