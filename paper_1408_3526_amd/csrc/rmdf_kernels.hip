@@ -41,6 +41,8 @@ __global__ void __launch_bounds__(256) k_row(const float* __restrict__ f, float2
   row_chunk<MX, DIRECT>(f, rs, twx, H, W, blockIdx.y, blockIdx.x * RCX, smem, nonfinite, slot);
 }
 
+// Four wavefronts per SIMD (two of 16x16x8).  No form has spills but the 8x8x4 one that
+// computes its own rows: 6 registers, 28 bytes a lane.
 template <int MX, int MY, int MZ, bool REFINED, bool OWN_ROWS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MZ == 8 ? 2 : 4))) k_pixel(PixArgs a) {
   using SH = Shape<MX, MY, MZ>;
