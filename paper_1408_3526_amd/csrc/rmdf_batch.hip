@@ -127,26 +127,26 @@ constexpr size_t MIXED_SMEM = cmax(cmax(KindSmem<KIND_884>::v, KindSmem<KIND_995
 constexpr bool in_mixed(int kind) { return kind != KIND_16G; }
 
 // The small tiles are called rather than inlined into the mixed kernel: each
-// keeps its own register allocation, and the 16x16x8 path (inlined) has no spills
-// (a call saves what the callee uses of its caller's registers, 8 bytes a lane).  A
-// called function's arguments are values per lane to the compiler, and a buffer
+// keeps its own register allocation, and the 16x16x8 path (inlined) has no spills.
+// A called function's arguments are values per lane to the compiler, and a buffer
 // access through a descriptor made from such values becomes a loop over the lanes'
-// descriptors (66 of them in the two tiles), so the arguments are made scalar again.
-static __device__ __forceinline__ PixArgs uniform_args(const PixArgs& a) {
+// descriptors (66 of them in the two tiles), so the arguments are made scalar again:
+// word by word, since an address taken apart to make it scalar could be written
+// through for all the kernel knows, and its own descriptors would then be read by
+// vector loads.
+static __device__ __forceinline__ PixArgs uniform(const PixArgs& a) {
   struct Words { unsigned w[sizeof(PixArgs) / 4]; };
   static_assert(sizeof(Words) == sizeof(PixArgs), "whole words");
-  typedef __attribute__((address_space(4))) const unsigned const_word;
-  const const_word* src = (const const_word*)uniform(reinterpret_cast<const unsigned*>(&a));
-  Words v;
+  Words v = __builtin_bit_cast(Words, a);
 #pragma unroll
-  for (unsigned i = 0; i < sizeof(PixArgs) / 4; ++i) v.w[i] = src[i];
+  for (unsigned i = 0; i < sizeof(PixArgs) / 4; ++i) v.w[i] = (unsigned)__builtin_amdgcn_readfirstlane((int)v.w[i]);
   return __builtin_bit_cast(PixArgs, v);
 }
 static __device__ __attribute__((noinline)) void tile884(const PixArgs& a, const float* rd, int xb, int yb, char* smem) {
-  pixel_tile<8, 8, 4>(uniform_args(a), uniform(rd), uniform(xb), uniform(yb), smem);
+  pixel_tile<8, 8, 4>(uniform(a), uniform(rd), uniform(xb), uniform(yb), smem);
 }
 static __device__ __attribute__((noinline)) void tile995(const PixArgs& a, const float* rd, int xb, int yb, char* smem) {
-  pixel_tile<9, 9, 5>(uniform_args(a), uniform(rd), uniform(xb), uniform(yb), smem);
+  pixel_tile<9, 9, 5>(uniform(a), uniform(rd), uniform(xb), uniform(yb), smem);
 }
 
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))

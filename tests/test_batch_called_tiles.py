@@ -2,7 +2,9 @@
 compiler takes their arguments for values per lane unless the code makes them
 scalar.  A buffer access through a descriptor of such values becomes a loop that
 reads one lane's descriptor at a time and compares it with the others'; the
-compiled tiles have none of these (no GPU needed)."""
+compiled tiles have none of these.  And the kernel itself reads its descriptors
+by scalar loads, which it does only while no call could write them (no GPU
+needed)."""
 import os
 import re
 import shutil
@@ -25,3 +27,6 @@ def test_called_tiles_use_scalar_descriptors(tmp_path):
     for name, body in bodies.items():
         assert "buffer_load" in body and "buffer_store" in body, name
         assert "v_cmp_eq_u64" not in body, (name, body.count("v_cmp_eq_u64"))
+    kernel, = re.findall(r"^_ZN4rmdf13k_batch_mixed\w*:(.*?)^\.Lfunc_end", text, re.M | re.S)
+    # (the frame counter is the one vector load by a global address)
+    assert len(re.findall(r"^\tglobal_load", kernel, re.M)) <= 2
