@@ -176,7 +176,8 @@ rmdf_status rmdf_push_frames(rmdf_ctx *ctx, int n, const float *const *frames_de
  * l_z = 1 slice (Sec. 2, flow paragraph and eq. 10); the per-pixel velocity
  * the detector hands on (Sec. 1).  A device-to-device copy on the context
  * stream; the buffers are the caller's.
- * Errors: RMDF_E_INVAL (NULL ctx), RMDF_E_STATE before the first push. */
+ * Errors: RMDF_E_INVAL (NULL ctx), RMDF_E_STATE before the first push,
+ * RMDF_E_DEVICE (a copy that HIP refuses, e.g. into too small an allocation). */
 rmdf_status rmdf_velocity(rmdf_ctx *ctx, float *vxy_dev, int *idx_dev);
 
 /* Copy the prediction-error output of the latest frame into out_dev[H*W].
